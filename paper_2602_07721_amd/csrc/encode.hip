@@ -18,11 +18,38 @@
 // Every float64 operation is an explicit round-to-nearest multiply or add
 // (no contraction), so the results do not depend on the compiler.
 //
-// Mapping: 4 lanes per key; lane q holds coordinates [32q, 32q+32), i.e.
-// subspaces 4q..4q+3.  Butterfly strides 1..16 are in registers, 32 and 64
-// cross lanes (partners q^1, q^2).  Each lane then writes its 4 id bytes and
-// the two 16-byte record chunks 2q and 2q+1.  Cluster counts are gathered in
-// an LDS histogram per block and added to global memory once per block.
+// Transform.  H (s (.) k) is a 128 x 128 matrix of +-1 times the keys: matrix
+// instructions (16x16x32, float16 in, float32 sums), made exact by splitting every
+// key coordinate x = hi + lo: lo = x less its rounding to a multiple of 2^-6 when
+// |x| < 8, else 0.  So |lo| <= 2^-7 in units of 2^-24 and 128 of them sum below
+// 2^24 units; |x| < 1024 gives hi in units of 2^-7 (2^-6 below 8) and a sum of at
+// most 2^24 of them.  Every partial sum of either part is then exact in float32 in
+// any order, and y = hi + lo in float64 is exact too.  lo is carried as 2^11 lo,
+// which is a normal float16 number.  A tile of 16 keys whose sums of squares may come from a
+// coordinate of 1024 or more (or are not finite) is redone by the float64 butterflies.
+//
+// Mapping: a wave takes 16 keys; lane 16 g + r holds coordinates [32 g, 32 g + 32) of
+// key r, i.e. subspaces 4g..4g+3, before and after the transform.  Coordinate 8 s +
+// 2 j + e (s < 16, j < 4, e < 2): a matrix step multiplies the 32 inputs of one j,
+// which lie in the 4 loaded uint4 as component j of each, so no data moves before
+// the product; output tile (J, T) holds (s, e) rows chosen so that lane group g gets
+// subspaces 4g + 2T, 4g + 2T + 1.
+//
+// Bins.  t_j compares Y_j with at most one of the 7 products tau_t^2 S_b: u = |y_j| /
+// sqrt(S_b) in float32 (error below 2^-20) falls in one of 64 buckets of [0, 1]; the
+// bucket's entry names the bins surely passed and the one threshold that is not decided,
+// which is then compared in float64 as defined above.  Buckets are far narrower than
+// the gaps between thresholds (0.08 at least).
+//
+// What bounds it: vector issue.  A 16-key tile is about 830 vector instructions and 64
+// matrix instructions (1665 vector ones with the transform as float64 butterflies and 7
+// compares per coordinate); the vector unit is busy 74% of the time with 3 waves per SIMD.
+// Measured: 8 x 131072 keys 238 -> 150 us (2.8 TB/s), 24 x 10007 keys 177 -> 45 us, most of
+// the second from blocks sized to fill the chip (launch_encode).  Two waves per SIMD, with
+// the matrix operands held in registers, took 14% longer.
+//
+// Each lane counts its 4 ids in an LDS histogram per block, added to global memory
+// once per block; records go through LDS so that a wave stores whole lines.
 
 #include <hip/hip_fp16.h>
 
@@ -36,7 +63,42 @@ namespace pariskv {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kKeysPerIter = kThreads / 4;
+constexpr int kTile = 16;                           // keys per wave and iteration
+constexpr int kKeysPerIter = kThreads / 64 * kTile;
+constexpr int kBuckets = 64;                        // of u in [0, 1]; u may round up to 1: one more entry
+constexpr int kBucketLut = kBuckets + 1;
+constexpr int kFrags = 14;                          // matrix operands: 2 tiles x 4 steps, 3 of them also negated
+constexpr int kStageRow = kRec + 16;                // bytes per staged record (padded against bank conflicts)
+
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f16x2 as_f16x2(uint32_t w) { return __builtin_bit_cast(f16x2, w); }
+__device__ __forceinline__ uint32_t as_u32(f16x2 h) { return __builtin_bit_cast(uint32_t, h); }
+
+__device__ __forceinline__ uint32_t pk_clamp8(uint32_t w) {
+    uint32_t r;
+    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(w), "v"(0x48004800u));
+    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(r), "v"(0xC800C800u));
+    return r;
+}
+
+// Two coordinates as (hi, 2^11 lo), see the transform above.
+__device__ __forceinline__ void split_pair(uint32_t w, uint32_t* hi, uint32_t* lo) {
+    const f16x2 x = as_f16x2(w), xc = as_f16x2(pk_clamp8(w));
+    const f16x2 magic = as_f16x2(0x4E004E00u);   // 24: the sum with |xc| <= 8 rounds to multiples of 2^-6
+    const f16x2 t = xc + magic;
+    // -2^11 (t - 24), then 2^11 (xc - (t - 24)); each exact
+    const f16x2 nr = __builtin_elementwise_fma(t, as_f16x2(0xE800E800u), as_f16x2(0x7A007A00u));
+    const f16x2 l = __builtin_elementwise_fma(xc, as_f16x2(0x68006800u), nr);
+    *lo = as_u32(l);
+    *hi = as_u32(__builtin_elementwise_fma(l, as_f16x2(0x90009000u), x));  // x - lo
+}
+
+__device__ __forceinline__ f16x8 frag(const uint32_t (&w)[4]) {
+    return __builtin_bit_cast(f16x8, make_uint4(w[0], w[1], w[2], w[3]));
+}
 
 __device__ __forceinline__ double tree8_sum(const double* v) {
     double s01 = __dadd_rn(v[0], v[1]);
@@ -46,145 +108,347 @@ __device__ __forceinline__ double tree8_sum(const double* v) {
     return __dadd_rn(__dadd_rn(s01, s23), __dadd_rn(s45, s67));
 }
 
-template <bool kLdsCounts>
-__global__ __launch_bounds__(kThreads) void encode_kernel(
+// id_slot of the 4 bytes of a word.
+__device__ __forceinline__ uint32_t id_slot4(uint32_t w) {
+    const uint32_t b5 = (w >> 5) & 0x01010101u, b6 = (w >> 6) & 0x01010101u, b7 = (w >> 7) & 0x01010101u;
+    return w ^ ((b5 << 3) - b5) ^ (b6 | b6 << 3 | b6 << 4) ^ ((b7 << 4) - (b7 << 1));
+}
+
+// Both float16 of a word as float64.
+__device__ __forceinline__ void widen(uint32_t w, double* lo, double* hi) {
+    *lo = (double)__half2float(__ushort_as_half((unsigned short)(w & 0xffffu)));
+    *hi = (double)__half2float(__ushort_as_half((unsigned short)(w >> 16)));
+}
+
+// Per bucket of u: the next threshold (tau^2) and the bins surely passed, both 8 bytes apart
+// so that one address serves the two reads.
+struct Buckets {
+    double next[kBucketLut];
+    uint32_t passed[kBucketLut][2];
+};
+
+// One subspace's summary: id (bit j = [y_j < 0]), code word, weight.
+struct Summary {
+    uint32_t id, code;
+    float w;
+};
+
+// Without the alpha-correction the weight is ||y_b|| = sqrt(S_b).
+template <bool kAlpha>
+__device__ __forceinline__ float weight(double S, double A) {
+    const float w = kAlpha ? (float)(S / A) : (float)__dsqrt_rn(S);
+    return S > 0.0 ? w : 0.0f;
+}
+
+// Any y: 7 compares per coordinate.
+template <bool kAlpha>
+__device__ __forceinline__ Summary summarise_any(const double* y, double S, const double* tau2, const double* s_a) {
+    double TS[7], P[8];
+#pragma unroll
+    for (int t = 0; t < 7; ++t) TS[t] = __dmul_rn(tau2[t], S);
+    const bool nz = S > 0.0;
+    Summary r{0u, 0u, 0.0f};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const double Y = __dmul_rn(y[j], y[j]);
+        const uint32_t neg = y[j] < 0.0 ? 1u : 0u;
+        uint32_t t = 0;
+#pragma unroll
+        for (int u = 0; u < 7; ++u) t += (Y >= TS[u]) ? 1u : 0u;
+        t = nz ? t : 0u;
+        P[j] = __dmul_rn(s_a[t], fabs(y[j]));
+        r.id |= neg << j;
+        r.code |= (neg << 3 | t) << (4 * j);
+    }
+    r.w = weight<kAlpha>(S, tree8_sum(P));
+    return r;
+}
+
+// Finite y, none of them -0: one compare per coordinate, chosen by its bucket.
+template <bool kAlpha>
+__device__ __forceinline__ Summary summarise(const double* y, const double* Y, double S, const Buckets& s_bk, const double* s_a) {
+    // |u| kBuckets <= kBuckets (1 + 2^-20); S = 0 gives NaN, which converts to bucket 0.
+    const float rs = (float)kBuckets * __builtin_amdgcn_rsqf((float)S);
+    double P[8];
+    uint32_t code = 0;
+#pragma unroll
+    for (int j = 7; j >= 0; --j) {
+        uint32_t bucket;
+        asm("v_cvt_u32_f32 %0, %1" : "=v"(bucket) : "v"(fabsf((float)y[j]) * rs));
+        const uint32_t t = s_bk.passed[bucket][0] + (Y[j] >= __dmul_rn(s_bk.next[bucket], S) ? 1u : 0u);
+        P[j] = __dmul_rn(s_a[t], fabs(y[j]));
+        code = __builtin_amdgcn_alignbit(code, (uint32_t)__double2hiint(y[j]), 31);  // code << 1 | sign
+        code = code << 3 | t;
+    }
+    code = S > 0.0 ? code : 0u;
+    Summary r;
+    r.code = code;
+    // The sign bits 3, 7, .. 31 of the code word, gathered into a byte.
+    const uint32_t sg = code & 0x88888888u;
+    r.id = (__builtin_amdgcn_udot8(sg, 0x00008421u, 0u, false) >> 3) |
+           (__builtin_amdgcn_udot8(sg, 0x84210000u, 0u, false) << 1);
+    r.w = weight<kAlpha>(S, tree8_sum(P));
+    return r;
+}
+
+// The 64 bytes of coordinates [32 (lane / 16), +32) of key base + lane % 16 (zeros past the end).
+__device__ __forceinline__ void load_part(const __half* src, int64_t base, int64_t k_end, int lane, uint4 (&v)[4]) {
+    const int64_t i = base + (lane & 15);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = make_uint4(0, 0, 0, 0);
+    if (i < k_end) {
+        const uint4* p = reinterpret_cast<const uint4*>(src + i * kD + 32 * (lane >> 4));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = p[c];
+    }
+}
+
+// y of this lane's 32 coordinates by float64 butterflies: strides 1..16 in registers,
+// 32 and 64 across lanes (16 and 32 lanes away).
+__device__ __forceinline__ void butterflies(const uint4 (&raw)[4], uint32_t smask, int lane, double* x) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint32_t w[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
+#pragma unroll
+        for (int h = 0; h < 4; ++h) widen(w[h], &x[8 * c + 2 * h], &x[8 * c + 2 * h + 1]);
+    }
+#pragma unroll
+    for (int j = 0; j < 32; ++j)
+        if ((smask >> j) & 1u) x[j] = -x[j];
+#pragma unroll
+    for (int h = 1; h < 32; h <<= 1) {
+#pragma unroll
+        for (int j = 0; j < 32; ++j) {
+            if ((j & h) == 0) {
+                const double a0 = x[j], a1 = x[j + h];
+                x[j] = __dadd_rn(a0, a1);
+                x[j + h] = __dsub_rn(a0, a1);
+            }
+        }
+    }
+#pragma unroll
+    for (int m = 16; m <= 32; m <<= 1) {
+        const bool upper = (lane & m) != 0;
+#pragma unroll
+        for (int j = 0; j < 32; ++j) {
+            const double p = __shfl_xor(x[j], m, 64);
+            x[j] = upper ? __dsub_rn(p, x[j]) : __dadd_rn(x[j], p);
+            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // few exchanges in flight: registers
+        }
+    }
+}
+
+struct Summaries {
+    Summary s[4];
+};
+
+// This lane's 4 subspaces of key base + lane % 16 by the float64 butterflies: any keys.  Not
+// inlined: it is rare, and its registers would be the kernel's.
+template <bool kAlpha>
+__device__ __attribute__((noinline)) Summaries general_tile(const __half* src, int64_t base, int64_t k_end,
+                                                            uint32_t smask, const double* s_a, const QuantConsts& qc) {
+    const int lane = threadIdx.x & 63;
+    uint4 raw[4];
+    load_part(src, base, k_end, lane, raw);
+    double x[32];
+    butterflies(raw, smask, lane, x);
+    Summaries r;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        double Y[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) Y[j] = __dmul_rn(x[8 * b + j], x[8 * b + j]);
+        r.s[b] = summarise_any<kAlpha>(x + 8 * b, tree8_sum(Y), qc.tau2, s_a);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return r;
+}
+
+template <bool kLdsCounts, bool kRotate, bool kAlpha>
+__global__ __launch_bounds__(kThreads, 3) void encode_kernel(
     const __half* __restrict__ keys, int64_t n_src, int64_t src_stride, int64_t keys_per_block, int64_t row0,
     int64_t capacity, uint8_t* __restrict__ ids, uint8_t* __restrict__ rec,
-    uint32_t* __restrict__ counts, SignBits sb, QuantConsts qc, uint32_t flags) {
+    uint32_t* __restrict__ counts, SignBits sb, QuantConsts qc) {
     __shared__ double s_a[8];
+    __shared__ Buckets s_bk;
+    __shared__ uint4 s_frag[kRotate ? kFrags : 1][64];
+    __shared__ __align__(16) uint8_t s_stage[kThreads / 64][kTile * kStageRow];
     __shared__ uint32_t s_cnt[kLdsCounts ? kB * kCentroids : 1];
 
     const int tid = threadIdx.x;
-    const int q = tid & 3;
-    const int slot = tid >> 2;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int waves = (int)blockDim.x >> 6;
+    const int g = lane >> 4, r16 = lane & 15;
     const int64_t grp = blockIdx.y;
     const int64_t k_begin = (int64_t)blockIdx.x * keys_per_block;
     const int64_t k_end = min(k_begin + keys_per_block, n_src);
 
+    const __half* src = keys + grp * src_stride * kD;
+    uint4 raw[4];
+    load_part(src, k_begin + wave * kTile, k_end, lane, raw);
+
+    const uint32_t smask = g == 0 ? sb.w[0] : g == 1 ? sb.w[1] : g == 2 ? sb.w[2] : sb.w[3];
+    // Matrix operands, one uint4 per lane: output (s, e) of tile T in row r16, inputs
+    // 8 (4g + c) + 2 j + e', the rotation's signs folded in.  Tile (J, T) takes step j as it is
+    // or negated (odd popcount of J & j).
+    if (kRotate) {
+        for (int f = wave; f < 8; f += waves) {
+            const int T = f >> 2, j = f & 3;
+            const int so = 4 * (r16 >> 2) + 2 * T + ((r16 >> 1) & 1);
+            uint32_t w[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t b = smask >> (8 * c + 2 * j);
+                w[c] = (0x3C003C00u | (b & 1u) << 15 | (b & 2u) << 30) ^
+                       (__popc(so & (4 * g + c)) & 1 ? 0x80008000u : 0u) ^ (r16 & 1 ? 0x80000000u : 0u);
+            }
+            s_frag[f][lane] = make_uint4(w[0], w[1], w[2], w[3]);
+            if (j)
+                s_frag[8 + 3 * T + j - 1][lane] = make_uint4(w[0] ^ 0x80008000u, w[1] ^ 0x80008000u,
+                                                             w[2] ^ 0x80008000u, w[3] ^ 0x80008000u);
+        }
+    }
     if (tid < 8) s_a[tid] = qc.a[tid];
+    for (int i = tid; i < kBucketLut; i += (int)blockDim.x) {
+        // Bins surely passed by every u that may fall in bucket i, and the next threshold.
+        const double lo = fmax(0.0, ((double)i - 1e-3) / kBuckets);
+        uint32_t c = 0;
+        double next = __builtin_huge_val();
+#pragma unroll
+        for (int t = 6; t >= 0; --t) {
+            const bool passed = qc.tau2[t] <= lo * lo;
+            c += passed ? 1u : 0u;
+            next = passed ? next : qc.tau2[t];
+        }
+        s_bk.next[i] = next;
+        s_bk.passed[i][0] = c;
+    }
     if (kLdsCounts) {
-        for (int i = tid; i < kB * kCentroids; i += kThreads) s_cnt[i] = 0;
+        for (int i = tid; i < kB * kCentroids; i += (int)blockDim.x) s_cnt[i] = 0;
     }
     __syncthreads();
 
-    const uint32_t smask = sb.w[q];
-    double tau2[7];
+    for (int64_t base = k_begin + wave * kTile; base < k_end; base += waves * kTile) {
+        uint4 cur[4];
 #pragma unroll
-    for (int t = 0; t < 7; ++t) tau2[t] = qc.tau2[t];
+        for (int c = 0; c < 4; ++c) cur[c] = raw[c];
+        load_part(src, base + waves * kTile, k_end, lane, raw);  // the next tile's keys arrive under this one's work
 
-    for (int64_t base = k_begin; base < k_end; base += kKeysPerIter) {
-        const int64_t i = base + slot;
-        const bool live = i < k_end;
-        // Out-of-range lanes still join the shuffles (with zeros) and store nothing.
-        double x[32];
-        if (live) {
-            const uint4* src = reinterpret_cast<const uint4*>(keys + ((grp * src_stride + i) * kD + 32 * q));
+        Summary sm[4];
+        double total = 0.0;  // sum of squares of this lane's y
+        if (kRotate) {
+            uint32_t hi[4][4], lo[4][4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                uint4 v = src[c];
-                uint32_t w[4] = {v.x, v.y, v.z, v.w};
+                split_pair(cur[c].x, &hi[0][c], &lo[0][c]);
+                split_pair(cur[c].y, &hi[1][c], &lo[1][c]);
+                split_pair(cur[c].z, &hi[2][c], &lo[2][c]);
+                split_pair(cur[c].w, &hi[3][c], &lo[3][c]);
+            }
+            // Read for every tile: 56 registers less than holding them, which is another wave per SIMD.
+            int at = lane;
+            asm volatile("" : "+v"(at));
 #pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    __half lo = __ushort_as_half((unsigned short)(w[h] & 0xffffu));
-                    __half hi = __ushort_as_half((unsigned short)(w[h] >> 16));
-                    x[8 * c + 2 * h] = (double)__half2float(lo);
-                    x[8 * c + 2 * h + 1] = (double)__half2float(hi);
+            for (int T = 0; T < 2; ++T) {
+                f16x8 A[4], N[3];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) A[j] = __builtin_bit_cast(f16x8, s_frag[4 * T + j][at]);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) N[j] = __builtin_bit_cast(f16x8, s_frag[8 + 3 * T + j][at]);
+                f32x4 ah[4], al[4];
+#pragma unroll
+                for (int J = 0; J < 4; ++J) {
+                    ah[J] = al[J] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const f16x8 m = (__builtin_popcount(J & j) & 1) ? N[j ? j - 1 : 0] : A[j];
+                        ah[J] = __builtin_amdgcn_mfma_f32_16x16x32_f16(m, frag(hi[j]), ah[J], 0, 0, 0);
+                        al[J] = __builtin_amdgcn_mfma_f32_16x16x32_f16(m, frag(lo[j]), al[J], 0, 0, 0);
+                    }
                 }
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    double y[8], Y[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        y[j] = __fma_rn((double)al[j >> 1][2 * q + (j & 1)], 0x1p-11, (double)ah[j >> 1][2 * q + (j & 1)]);
+                        Y[j] = __dmul_rn(y[j], y[j]);
+                    }
+                    const double S = tree8_sum(Y);
+                    total += S;
+                    sm[2 * T + q] = summarise<kAlpha>(y, Y, S, s_bk, s_a);
+                }
+                __builtin_amdgcn_sched_barrier(0);  // the halves of a tile share registers
+            }
+            // A coordinate of 1024 makes the key's squares sum to 2^27 over its 4 lanes.
+            if (__any(!(total < 0x1p24))) {
+                const Summaries again = general_tile<kAlpha>(src, base, k_end, smask, s_a, qc);
+#pragma unroll
+                for (int b = 0; b < 4; ++b) sm[b] = again.s[b];
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < 32; ++j) x[j] = 0.0;
-        }
-        if (!(flags & kFlagNoRotation)) {
+            for (int b = 0; b < 4; ++b) {
+                const uint32_t w[4] = {cur[b].x, cur[b].y, cur[b].z, cur[b].w};
+                double y[8], Y[8];
 #pragma unroll
-            for (int j = 0; j < 32; ++j)
-                if ((smask >> j) & 1u) x[j] = -x[j];
-
-            // In-register butterflies, strides 1..16 (exact).
+                for (int h = 0; h < 4; ++h) widen(w[h], &y[2 * h], &y[2 * h + 1]);
 #pragma unroll
-            for (int h = 1; h < 32; h <<= 1) {
-#pragma unroll
-                for (int j = 0; j < 32; ++j) {
-                    if ((j & h) == 0) {
-                        double a0 = x[j], a1 = x[j + h];
-                        x[j] = __dadd_rn(a0, a1);
-                        x[j + h] = __dsub_rn(a0, a1);
-                    }
-                }
-            }
-            // Cross-lane butterflies, strides 32 (lane q^1) and 64 (lane q^2).
-#pragma unroll
-            for (int m = 1; m <= 2; m <<= 1) {
-                const bool upper = (q & m) != 0;
-#pragma unroll
-                for (int j = 0; j < 32; ++j) {
-                    double p = __shfl_xor(x[j], m, 64);
-                    x[j] = upper ? __dsub_rn(p, x[j]) : __dadd_rn(x[j], p);
-                }
+                for (int j = 0; j < 8; ++j) Y[j] = __dmul_rn(y[j], y[j]);
+                sm[b] = summarise_any<kAlpha>(y, tree8_sum(Y), qc.tau2, s_a);
             }
         }
 
-        uint32_t id_word = 0, slot_word = 0;  // true ids (for counts), stored slots
-        uint32_t code[4];
-        float wgt[4];
+        uint8_t* stage = s_stage[wave];
+        uint4* st = reinterpret_cast<uint4*>(stage + r16 * kStageRow + 32 * g);
+        st[0] = make_uint4(sm[0].code, sm[1].code, __float_as_uint(sm[0].w), __float_as_uint(sm[1].w));
+        st[1] = make_uint4(sm[2].code, sm[3].code, __float_as_uint(sm[2].w), __float_as_uint(sm[3].w));
+        const int64_t row = grp * capacity + row0 + base;
+        if (base + r16 < k_end) {
+            *reinterpret_cast<uint32_t*>(ids + (row + r16) * kB + 4 * g) =
+                id_slot4(sm[0].id | sm[1].id << 8 | sm[2].id << 16 | sm[3].id << 24);
 #pragma unroll
-        for (int sbi = 0; sbi < 4; ++sbi) {
-            const double* y = x + 8 * sbi;
-            double Y[8], P[8];
-            uint32_t idb = 0, cw = 0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                Y[j] = __dmul_rn(y[j], y[j]);
-                idb |= (y[j] < 0.0 ? 1u : 0u) << j;
-            }
-            const double S = tree8_sum(Y);
-            double TS[7];
-#pragma unroll
-            for (int t = 0; t < 7; ++t) TS[t] = __dmul_rn(tau2[t], S);
-            const bool nz = S > 0.0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                uint32_t t = 0;
-#pragma unroll
-                for (int u = 0; u < 7; ++u) t += (Y[j] >= TS[u]) ? 1u : 0u;
-                t = nz ? t : 0u;
-                P[j] = __dmul_rn(s_a[t], fabs(y[j]));
-                cw |= ((((idb >> j) & 1u) << 3) | t) << (4 * j);
-            }
-            const double A = tree8_sum(P);
-            // Without the alpha-correction the weight is ||y_b|| = sqrt(S_b).
-            wgt[sbi] = !nz ? 0.0f : (flags & kFlagNoAlpha) ? (float)__dsqrt_rn(S) : (float)(S / A);
-            code[sbi] = cw;
-            id_word |= idb << (8 * sbi);
-            slot_word |= id_slot(idb) << (8 * sbi);
-        }
-
-        if (live) {
-            const int64_t row = grp * capacity + row0 + i;
-            *reinterpret_cast<uint32_t*>(ids + row * kB + 4 * q) = slot_word;
-            uint4* dst = reinterpret_cast<uint4*>(rec + row * kRec + 32 * q);
-            dst[0] = make_uint4(code[0], code[1], __float_as_uint(wgt[0]), __float_as_uint(wgt[1]));
-            dst[1] = make_uint4(code[2], code[3], __float_as_uint(wgt[2]), __float_as_uint(wgt[3]));
-#pragma unroll
-            for (int sbi = 0; sbi < 4; ++sbi) {
-                const int b = 4 * q + sbi;
-                const uint32_t c = (id_word >> (8 * sbi)) & 0xffu;
+            for (int b = 0; b < 4; ++b) {
+                const int at = (4 * g + b) * kCentroids + (int)sm[b].id;
                 if (kLdsCounts)
-                    atomicAdd(&s_cnt[b * kCentroids + c], 1u);
+                    atomicAdd(&s_cnt[at], 1u);
                 else
-                    atomicAdd(&counts[grp * (kB * kCentroids) + b * kCentroids + c], 1u);
+                    atomicAdd(&counts[grp * (kB * kCentroids) + at], 1u);
             }
         }
+        // The wave's own staged rows (LDS operations of a wave complete in order).
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int k = 8 * p + (lane >> 3);
+            const uint4 v = *reinterpret_cast<const uint4*>(stage + k * kStageRow + 16 * (lane & 7));
+            if (base + k < k_end) *reinterpret_cast<uint4*>(rec + (row + k) * kRec + 16 * (lane & 7)) = v;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 
     if (kLdsCounts) {
         __syncthreads();
-        for (int i = tid; i < kB * kCentroids; i += kThreads) {
+        for (int i = tid; i < kB * kCentroids; i += (int)blockDim.x) {
             const uint32_t v = s_cnt[i];
             if (v) atomicAdd(&counts[grp * (kB * kCentroids) + i], v);
         }
     }
 }
+
+// Blocks that run at once (3 per CU by registers).  Keys are dealt evenly over the fewest
+// whole rounds of that many blocks with at most 2048 keys each, so that no round is partly
+// empty; 64 keys are one step of a block.
+constexpr int64_t kFillBlocks = 768;
+constexpr int64_t kMaxKeysPerBlock = 2048;
+// Calls of at most one tile per group count straight into global memory.  Scattered global
+// atomics run at about 22 per ns over the chip (64 groups x 600 keys: 28 us with them, 18 us
+// through LDS); for one tile the LDS histogram costs more to clear and flush than it saves.
+constexpr int64_t kDirectCountKeys = 16;
 
 __global__ void zero_u32_kernel(uint32_t* p, int64_t count) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -207,21 +471,27 @@ hipError_t launch_encode(const void* keys, int64_t n_src, int64_t src_stride, in
                          hipStream_t s) {
     if (n_src <= 0 || groups <= 0) return hipSuccess;
     const __half* k = static_cast<const __half*>(keys);
-    if (n_src >= 1024) {
-        // Bulk: blocks of 2048 keys share one LDS histogram flush.
-        const int64_t per = 2048;
-        const int64_t bx = (n_src + per - 1) / per;
-        const ProfEvents pe = prof_begin("encode");
-        hipExtLaunchKernelGGL(encode_kernel<true>, dim3((unsigned)bx, (unsigned)groups), dim3(kThreads),
-                           0, s, pe.start, pe.stop, 0, k, n_src, src_stride, per, row0, capacity, ids, rec, counts, sb, qc, flags);
-    } else {
-        // Streaming append: few keys per group, count straight into global memory.
-        const int64_t per = kKeysPerIter;
-        const int64_t bx = (n_src + per - 1) / per;
-        const ProfEvents pe = prof_begin("append");
-        hipExtLaunchKernelGGL(encode_kernel<false>, dim3((unsigned)bx, (unsigned)groups), dim3(kThreads),
-                           0, s, pe.start, pe.stop, 0, k, n_src, src_stride, per, row0, capacity, ids, rec, counts, sb, qc, flags);
-    }
+    const bool rotate = !(flags & kFlagNoRotation), alpha = !(flags & kFlagNoAlpha);
+    const int64_t total = n_src * groups;
+    const int64_t fill = kFillBlocks * ((total + kFillBlocks * kMaxKeysPerBlock - 1) / (kFillBlocks * kMaxKeysPerBlock));
+    int64_t per = (total + fill - 1) / fill;
+    per = (per + kKeysPerIter - 1) / kKeysPerIter * kKeysPerIter;
+    const bool lds = n_src > kDirectCountKeys;
+    const dim3 grid((unsigned)((n_src + per - 1) / per), (unsigned)groups);
+    const dim3 block(kThreads);
+    const ProfEvents pe = prof_begin(lds ? "encode" : "append");
+#define PARISKV_ENCODE(LDS, ROT, ALPHA)                                                                   \
+    hipExtLaunchKernelGGL((encode_kernel<LDS, ROT, ALPHA>), grid, block, 0, s, pe.start, pe.stop, 0, k, n_src,   \
+                          src_stride, per, row0, capacity, ids, rec, counts, sb, qc)
+#define PARISKV_ENCODE_FLAGS(LDS)                                       \
+    (rotate ? (alpha ? PARISKV_ENCODE(LDS, true, true) : PARISKV_ENCODE(LDS, true, false)) \
+            : (alpha ? PARISKV_ENCODE(LDS, false, true) : PARISKV_ENCODE(LDS, false, false)))
+    if (lds)
+        PARISKV_ENCODE_FLAGS(true);
+    else
+        PARISKV_ENCODE_FLAGS(false);
+#undef PARISKV_ENCODE_FLAGS
+#undef PARISKV_ENCODE
     return hipGetLastError();
 }
 
