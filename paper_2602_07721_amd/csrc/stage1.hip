@@ -295,8 +295,14 @@ __global__ __launch_bounds__(kLutThreads) void query_lut_kernel(RetrieveArgs a) 
 
 // ---------------------------------------------------------------- collision scan
 
-constexpr int kColThreads = 256;
+// 512 threads: a block reads its 4096 keys in 2 rounds instead of the 4 of 256 threads, and
+// 4 blocks fill a CU.  Measured against 256: one block per CU or fewer 8.2 -> 6.6 us (1 x 8
+// rows of 4096 keys), 384 blocks 11.9 -> 11.7, 2048 blocks (8 x 8 x 131072 keys) 35.5 ->
+// 34.8, 8 x 3M keys 99 -> 95; 1024 threads are slower from 384 blocks on.
+constexpr int kColThreads = 512;
 constexpr int kColKeysPerIter = 4 * kColThreads;  // 4 keys per thread per iteration
+constexpr int kTableRows = kB * kCentroids / 4 / kColThreads;  // 16-byte table rows per thread
+static_assert(kTableRows * kColThreads * 4 == kB * kCentroids && kChunk % kColKeysPerIter == 0, "whole rounds");
 // Scores >= 1 go to one of two histogram copies picked by lane & 1 (fewer
 // same-address atomics per instruction), one 32-bit counter per (copy, head, value);
 // #{S >= 0} is the chunk's key count.
@@ -351,14 +357,13 @@ __global__ __launch_bounds__(kColThreads) void collide_kernel(RetrieveArgs a) {
     const int64_t row0 = (int64_t)seq * a.hq + kvh * a.g + 4 * quad;  // row of head 0 of the quad
 
     // The bonus table: every load in flight before the first LDS store.
-    static_assert(kB * kCentroids / 4 == 4 * kColThreads, "four 16-byte table rows per thread");
     const uint4* lsrc = reinterpret_cast<const uint4*>(a.lut + gq * (kB * kCentroids)) + tid;
-    const uint4 t0 = lsrc[0], t1 = lsrc[kColThreads], t2 = lsrc[2 * kColThreads], t3 = lsrc[3 * kColThreads];
+    uint4 row[kTableRows];
+#pragma unroll
+    for (int r = 0; r < kTableRows; ++r) row[r] = lsrc[r * kColThreads];
     uint4* ldst = reinterpret_cast<uint4*>(s_lut) + tid;
-    ldst[0] = t0;
-    ldst[kColThreads] = t1;
-    ldst[2 * kColThreads] = t2;
-    ldst[3 * kColThreads] = t3;
+#pragma unroll
+    for (int r = 0; r < kTableRows; ++r) ldst[r * kColThreads] = row[r];
     for (int i = tid; i < kHistCopies * 4 * kHistStride; i += kColThreads) s_hist[i] = 0;
     // Histogram floor of each head (a slot past the quad's last head scores 0: none).
     if (tid < 4) s_floor[tid] = tid < nh ? hist_floor(a.stats + (row0 + tid) * (kB * 2), a.n, a.c_eff, a.flags)
@@ -389,7 +394,7 @@ __global__ __launch_bounds__(kColThreads) void collide_kernel(RetrieveArgs a) {
     uint32_t* hcopy = s_hist + (lane & (kHistCopies - 1)) * (4 * kHistStride);
 
     for (uint32_t base = 0; base < nkeys; base += kColKeysPerIter) {
-        // Key base + tid + 256 j: one 16-byte id row per lane, a wave reads 1 KiB contiguous.
+        // Key base + tid + 512 j: one 16-byte id row per lane, a wave reads 1 KiB contiguous.
         uint4 w[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -684,8 +689,8 @@ hipError_t launch_query_lut(const RetrieveArgs& a, hipStream_t s) {
 
 hipError_t launch_collide(const RetrieveArgs& a, hipStream_t s) {
     const ProfEvents pe = prof_begin("collide");
-    hipExtLaunchKernelGGL(collide_kernel, dim3((unsigned)a.n_chunks, (unsigned)(a.batch * a.hkv * a.quads)),
-                       dim3(kColThreads), 0, s, pe.start, pe.stop, 0, a);
+    const dim3 grid((unsigned)a.n_chunks, (unsigned)(a.batch * a.hkv * a.quads));
+    hipExtLaunchKernelGGL(collide_kernel, grid, dim3(kColThreads), 0, s, pe.start, pe.stop, 0, a);
     return hipGetLastError();
 }
 

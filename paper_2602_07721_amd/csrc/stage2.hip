@@ -12,7 +12,8 @@
 // grids take blocks of 128 threads (32 keys per thread), so that 16 blocks
 // share a CU and their selection phases hide under each other's gathers; a
 // grid that fits the chip in one round of 256-thread blocks takes those (16
-// keys per thread), which halves each block's serial work.  It selects the chunk's candidates
+// keys per thread), which halves each block's serial work, and a smaller one
+// 512-thread blocks.  It selects the chunk's candidates
 // (all S > theta, then S == theta in ascending key order while the row's quota
 // lasts), which occupy consecutive positions of the row's candidate list,
 // writes them (and keeps them in LDS as 16-bit offsets in the chunk), and
@@ -47,8 +48,10 @@ namespace pariskv {
 namespace {
 
 // One 4096-key chunk per block: 128 threads for large grids, 256 for grids of at
-// most kRrWideGrid blocks (8 such blocks per CU on 256 CUs: one round).
-constexpr int kRrWideGrid = 2048;
+// most kRrWideGrid blocks (8 such blocks per CU on 256 CUs: one round), 512 up to
+// kRrWidestGrid blocks (2 per CU: each block's serial selection counts; 256 blocks of 32K-key
+// rows 7.6 -> 6.4 us, 8 blocks 8.9 -> 6.2, 512 blocks 8.8 -> 8.4, but 1024 blocks 11.5 -> 12.0).
+constexpr int64_t kRrWideGrid = 2048, kRrWidestGrid = 512;
 static_assert(kTopkPart >= PARISKV_MAX_TOPK, "a top-k slice holds at least k candidates");
 static_assert(PARISKV_MAX_CAND / kTopkPart * PARISKV_MAX_TOPK <= 1024 * 32, "the slices' winners fit one block");
 constexpr int kRrUnroll = 4;  // records in flight per lane
@@ -73,7 +76,8 @@ template <int kRrThreads>
 __global__ __launch_bounds__(kRrThreads) void compact_rerank_kernel(RetrieveArgs a) {
     constexpr int kKpt = kChunk / kRrThreads;   // keys per thread
     constexpr int kRrSlots = kRrThreads / 8;    // candidates reranked per block iteration
-    static_assert(kKpt % 16 == 0 && kKpt <= 32, "whole 16-byte score loads, one 32-bit mask");
+    constexpr int kWords = kKpt / 4;            // score words per thread
+    static_assert(kKpt >= 4 && kKpt <= 32, "whole score words, one 32-bit mask");
     __shared__ float s_tab[16];
     __shared__ uint32_t s_wsum[kRrThreads / 64];
     // The selected keys as offsets in the chunk (2 bytes each, so 16 blocks fit a CU).
@@ -96,11 +100,27 @@ __global__ __launch_bounds__(kRrThreads) void compact_rerank_kernel(RetrieveArgs
     // This thread's kKpt keys; score rows are padded to a multiple of 64 bytes, so a
     // load that starts before n stays inside the row.
     const int64_t i0 = chunk * kChunk + kKpt * tid;
-    uint4 sw[kKpt / 16];
+    uint32_t ww[kWords];
+    {
+        const uint8_t* sp = a.score8 + row * a.n_pad + i0;
+        if constexpr (kWords >= 4) {
 #pragma unroll
-    for (int u = 0; u < kKpt / 16; ++u) {
-        sw[u] = make_uint4(0, 0, 0, 0);
-        if (i0 + 16 * u < a.n) sw[u] = *reinterpret_cast<const uint4*>(a.score8 + row * a.n_pad + i0 + 16 * u);
+            for (int u = 0; u < kWords / 4; ++u) {
+                uint4 t = make_uint4(0, 0, 0, 0);
+                if (i0 + 16 * u < a.n) t = reinterpret_cast<const uint4*>(sp)[u];
+                ww[4 * u] = t.x;
+                ww[4 * u + 1] = t.y;
+                ww[4 * u + 2] = t.z;
+                ww[4 * u + 3] = t.w;
+            }
+        } else if constexpr (kWords == 2) {
+            uint2 t = make_uint2(0, 0);
+            if (i0 < a.n) t = *reinterpret_cast<const uint2*>(sp);
+            ww[0] = t.x;
+            ww[1] = t.y;
+        } else {
+            ww[0] = i0 < a.n ? *reinterpret_cast<const uint32_t*>(sp) : 0u;
+        }
     }
     const int l = tid & 7;
     float z[16];
@@ -117,14 +137,6 @@ __global__ __launch_bounds__(kRrThreads) void compact_rerank_kernel(RetrieveArgs
     // ---- compaction: all S > theta, and S == theta while the row's quota lasts.
     uint32_t gmask = 0, emask = 0;
     {
-        uint32_t ww[kKpt / 4];
-#pragma unroll
-        for (int u = 0; u < kKpt / 16; ++u) {
-            ww[4 * u] = sw[u].x;
-            ww[4 * u + 1] = sw[u].y;
-            ww[4 * u + 2] = sw[u].z;
-            ww[4 * u + 3] = sw[u].w;
-        }
 #pragma unroll
         for (int j = 0; j < kKpt; ++j) {
             const uint32_t sv = (ww[j >> 2] >> (8 * (j & 3))) & 0xffu;
@@ -880,7 +892,10 @@ __global__ void pad_outputs_kernel(int32_t* out_idx, float* out_score, int64_t c
 hipError_t launch_compact_rerank(const RetrieveArgs& a, hipStream_t s) {
     const ProfEvents pe = prof_begin("compact_rerank");
     const dim3 grid((unsigned)a.n_chunks, (unsigned)(a.batch * a.hq));
-    if ((int64_t)a.n_chunks * a.batch * a.hq <= kRrWideGrid)
+    const int64_t blocks = (int64_t)grid.x * grid.y;
+    if (blocks <= kRrWidestGrid)
+        hipExtLaunchKernelGGL(compact_rerank_kernel<512>, grid, dim3(512), 0, s, pe.start, pe.stop, 0, a);
+    else if (blocks <= kRrWideGrid)
         hipExtLaunchKernelGGL(compact_rerank_kernel<256>, grid, dim3(256), 0, s, pe.start, pe.stop, 0, a);
     else
         hipExtLaunchKernelGGL(compact_rerank_kernel<128>, grid, dim3(128), 0, s, pe.start, pe.stop, 0, a);
