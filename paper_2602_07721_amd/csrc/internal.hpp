@@ -114,6 +114,30 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
     return max(a, b);
 }
 
+// Suffix sums of a 97-bin histogram held as (lo = bins 0..63 by lane, hi = bins
+// 64..96 by lane < 33, 0 above): sfx[v] = sum_{u >= v} h[u], the total less the
+// exclusive prefix, from two DPP scans.  Returns (sfx_lo, sfx_hi).
+__device__ __forceinline__ void wave_suffix97(uint32_t lo, uint32_t hi, int lane, uint32_t* s_lo,
+                                              uint32_t* s_hi) {
+    const uint32_t ilo = wave_incl_sum(lo), ihi = wave_incl_sum(hi);
+    const uint32_t tlo = (uint32_t)__builtin_amdgcn_readlane((int)ilo, 63);
+    const uint32_t thi = (uint32_t)__builtin_amdgcn_readlane((int)ihi, 63);
+    *s_lo = thi + tlo - (ilo - lo);
+    *s_hi = thi - (ihi - hi);
+}
+
+// theta = largest v with #{S >= v} >= C, from a whole-row suffix histogram held as
+// (lo: v = lane, hi: v = 64 + lane), and gt = #{S > theta}.  Suffix counts fall with v
+// and #{S >= 0} = n >= C.
+__device__ __forceinline__ void theta_of(uint32_t ttl, uint32_t tth, uint32_t C, int lane, int* theta,
+                                         uint32_t* gt) {
+    const uint64_t ok_lo = __ballot(ttl >= C);
+    const uint64_t ok_hi = __ballot(lane < kBins - 64 && tth >= C);
+    const int th = ok_hi ? 64 + (63 - __clzll(ok_hi)) : (63 - __clzll(ok_lo));
+    *gt = th + 1 < 64 ? __shfl(ttl, th + 1, 64) : __shfl(tth, th + 1 - 64, 64);
+    *theta = th;
+}
+
 // Byte k of x shifted left (right) by 2 in one SDWA instruction: the byte
 // offset of table entry byte_k(x) (byte_k(x) >> 4) for 4-byte entries.
 template <int K>
@@ -256,6 +280,19 @@ struct RetrieveArgs {
     float* attn_out;
     AttendWindow win;  // dense rows attended next to the winners
 };
+
+// Grids of at most this many rerank blocks (chunks x rows) fit the chip in one round of
+// 256-thread blocks.
+constexpr int64_t kRrWideGrid = 2048;
+// Whether every rerank block derives its row's threshold itself, without a threshold launch.
+// Pays where the launch counts and few histograms are read: 1 x 8 heads x 4096 keys 33.7 ->
+// 31.3 us a call, 32 x 32K 35.3 -> 33.0, 256 x 32K (2048 blocks) 51.8 -> 49.0, 32 x 128K
+// (32 chunks) 44.7 -> 42.7.  Past one round of blocks the rerank's 128-thread blocks lose
+// what the launch saves (512 x 32K: 86.9 -> 88.5).
+constexpr int kFoldChunks = 32;
+inline bool fold_threshold(const RetrieveArgs& a) {
+    return a.n_chunks <= kFoldChunks && a.n_chunks * a.batch * a.hq <= kRrWideGrid;
+}
 
 hipError_t launch_query_lut(const RetrieveArgs& a, hipStream_t s);
 hipError_t launch_collide(const RetrieveArgs& a, hipStream_t s);

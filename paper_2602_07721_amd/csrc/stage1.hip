@@ -314,18 +314,6 @@ constexpr int kRawBufferWord3 = 0x00020000;
 // A buffer offset past every range: the access is dropped (stores) or reads 0 (loads).
 constexpr uint32_t kOffsetOutOfRange = 0x80000000u;
 
-// Suffix sums of a 97-bin histogram held as (lo = bins 0..63 by lane, hi = bins
-// 64..96 by lane < 33, 0 above): sfx[v] = sum_{u >= v} h[u], the total less the
-// exclusive prefix, from two DPP scans.  Returns (sfx_lo, sfx_hi).
-__device__ __forceinline__ void wave_suffix97(uint32_t lo, uint32_t hi, int lane, uint32_t* s_lo,
-                                              uint32_t* s_hi) {
-    const uint32_t ilo = wave_incl_sum(lo), ihi = wave_incl_sum(hi);
-    const uint32_t tlo = (uint32_t)__builtin_amdgcn_readlane((int)ilo, 63);
-    const uint32_t thi = (uint32_t)__builtin_amdgcn_readlane((int)ihi, 63);
-    *s_lo = thi + tlo - (ilo - lo);
-    *s_hi = thi - (ihi - hi);
-}
-
 __global__ __launch_bounds__(kColThreads) void collide_kernel(RetrieveArgs a) {
     __shared__ uint32_t s_lut[kB * kCentroids];
     __shared__ uint32_t s_hist[kHistCopies * 4 * kHistStride];
@@ -458,18 +446,6 @@ __global__ __launch_bounds__(kColThreads) void collide_kernel(RetrieveArgs a) {
 
 constexpr int kThrThreads = 1024;  // one block per query head
 constexpr int kThrWaves = kThrThreads / 64;
-
-// theta = largest v with #{S >= v} >= C, from a whole-row suffix histogram held as
-// (lo: v = lane, hi: v = 64 + lane), and gt = #{S > theta}.  Suffix counts fall with v
-// and #{S >= 0} = n >= C.
-__device__ __forceinline__ void theta_of(uint32_t ttl, uint32_t tth, uint32_t C, int lane, int* theta,
-                                         uint32_t* gt) {
-    const uint64_t ok_lo = __ballot(ttl >= C);
-    const uint64_t ok_hi = __ballot(lane < kBins - 64 && tth >= C);
-    const int th = ok_hi ? 64 + (63 - __clzll(ok_hi)) : (63 - __clzll(ok_lo));
-    *gt = th + 1 < 64 ? __shfl(ttl, th + 1, 64) : __shfl(tth, th + 1 - 64, 64);
-    *theta = th;
-}
 
 // kThrUnroll: chunks per wave and load round, the smallest power of two with
 // 16 kThrUnroll >= n_chunks (at most 16: a 1M-key row in one round).

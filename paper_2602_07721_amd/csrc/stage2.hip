@@ -51,7 +51,7 @@ namespace {
 // most kRrWideGrid blocks (8 such blocks per CU on 256 CUs: one round), 512 up to
 // kRrWidestGrid blocks (2 per CU: each block's serial selection counts; 256 blocks of 32K-key
 // rows 7.6 -> 6.4 us, 8 blocks 8.9 -> 6.2, 512 blocks 8.8 -> 8.4, but 1024 blocks 11.5 -> 12.0).
-constexpr int64_t kRrWideGrid = 2048, kRrWidestGrid = 512;
+constexpr int64_t kRrWidestGrid = 512;
 static_assert(kTopkPart >= PARISKV_MAX_TOPK, "a top-k slice holds at least k candidates");
 static_assert(PARISKV_MAX_CAND / kTopkPart * PARISKV_MAX_TOPK <= 1024 * 32, "the slices' winners fit one block");
 constexpr int kRrUnroll = 4;  // records in flight per lane
@@ -68,11 +68,122 @@ __device__ __forceinline__ float key_float(uint32_t k) {
     return __uint_as_float(u);
 }
 
+// What a block of the folded rerank derives for its row and chunk.
+struct RowSelect {
+    uint32_t theta, quota, base_g, base_e;
+};
+
+template <int TH>
+struct FoldScratch {
+    uint32_t part[TH / 64][4][64];  // per wave: row totals (v = lane, 64 + lane), totals before the chunk
+    uint32_t hist[2][kBins + 1];    // the recount's: whole row, before the chunk
+};
+
+// The selection threshold of row `row` and the chunk's bases, as the threshold kernel leaves
+// them (there one block per row does it for all chunks), for rows of at most kFoldChunks
+// chunks: see fold_threshold.  Every thread of the block calls it.  It costs the rerank 1 to
+// 2 us (a chunk histogram read and one more barrier, where the plain form waits for the
+// threshold's words) and saves a launch of 4.
+template <int TH>
+__device__ __forceinline__ RowSelect row_select(const RetrieveArgs& a, int64_t row, int64_t chunk,
+                                                FoldScratch<TH>& sm) {
+    constexpr int kWaves = TH / 64;
+    constexpr int kPer = kFoldChunks / kWaves;  // chunk histograms per wave
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t* sfx = a.chunk_sfx + row * a.n_chunks * kSfx;
+    int32_t* t = a.thresh + row * kThreshRow;
+    const uint32_t fl = (uint32_t)t[4];  // the floor the scan used
+    const int nc = (int)a.n_chunks, ck = (int)chunk;
+    // Every load is issued (clamped into the row) before the first wait.
+    uint32_t xl[kPer], xh[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int c = min(wave + kWaves * u, nc - 1);
+        xl[u] = sfx[c * kSfx + lane];
+        xh[u] = sfx[c * kSfx + 64 + min(lane, kSfx - 65)];
+    }
+    uint32_t tl = 0, thi = 0, bl = 0, bh = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int c = wave + kWaves * u;
+        const uint32_t l = c < nc ? xl[u] : 0u, h = c < nc && lane < kSfx - 64 ? xh[u] : 0u;
+        tl += l;
+        thi += h;
+        bl += c < ck ? l : 0u;
+        bh += c < ck ? h : 0u;
+    }
+    sm.part[wave][0][lane] = tl;
+    sm.part[wave][1][lane] = thi;
+    sm.part[wave][2][lane] = bl;
+    sm.part[wave][3][lane] = bh;
+    __syncthreads();
+    tl = thi = bl = bh = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        tl += sm.part[w][0][lane];
+        thi += sm.part[w][1][lane];
+        bl += sm.part[w][2][lane];
+        bh += sm.part[w][3][lane];
+    }
+    const uint32_t C = (uint32_t)a.c_eff;
+    // The counts are exact for v = 0 and v >= the floor: with #{S >= floor} >= C (or floor 1)
+    // theta is found among them, otherwise the row's scores are recounted.
+    const uint32_t at_floor = fl < 64 ? __shfl(tl, (int)fl, 64) : __shfl(thi, (int)fl - 64, 64);
+    const bool recount = fl > 1u && at_floor < C;
+    if (recount) {
+        for (int i = tid; i < 2 * (kBins + 1); i += TH) (&sm.hist[0][0])[i] = 0;
+        __syncthreads();
+        const uint8_t* srow = a.score8 + row * a.n_pad;
+        for (int64_t i = (int64_t)tid * 16; i < a.n; i += (int64_t)TH * 16) {
+            const uint4 w = *reinterpret_cast<const uint4*>(srow + i);  // i + 16 <= n_pad
+            const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+            const bool before = i < chunk * kChunk;  // a chunk is whole 16-byte words
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const uint32_t v = (ww[j >> 2] >> (8 * (j & 3))) & 0xffu;
+                if (i + j < a.n) {
+                    atomicAdd(&sm.hist[0][v], 1u);
+                    if (before) atomicAdd(&sm.hist[1][v], 1u);
+                }
+            }
+        }
+        __syncthreads();
+        wave_suffix97(sm.hist[0][lane], lane < kBins - 64 ? sm.hist[0][64 + lane] : 0u, lane, &tl, &thi);
+        wave_suffix97(sm.hist[1][lane], lane < kBins - 64 ? sm.hist[1][64 + lane] : 0u, lane, &bl, &bh);
+    }
+    int theta;
+    uint32_t gt;
+    theta_of(tl, thi, C, lane, &theta, &gt);
+    theta = __builtin_amdgcn_readfirstlane(theta);
+    auto before = [&](int v) {
+        return v < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)bl, v) : (uint32_t)__builtin_amdgcn_readlane((int)bh, v - 64);
+    };
+    RowSelect r;
+    r.theta = (uint32_t)theta;
+    r.quota = C - gt;
+    r.base_g = before(theta + 1);
+    r.base_e = before(theta) - r.base_g;
+    if (tid == 0) {
+        int32_t* cb = a.chunk_base + (row * a.n_chunks + chunk) * 2;
+        cb[0] = (int32_t)r.base_g;
+        cb[1] = (int32_t)r.base_e;
+        if (chunk == 0) {  // t[4] stays the scan's: the other blocks read it
+            t[0] = theta;
+            t[1] = (int32_t)gt;
+            t[2] = (int32_t)r.quota;
+            t[3] = (int32_t)C;
+            t[5] = recount ? 1 : 0;
+            t[6] = t[7] = 0;
+        }
+    }
+    return r;
+}
+
 // Compaction of one chunk's candidates (Stage I selection) fused with their
 // RSQ-IP rerank (Stage II).  The selected keys of a chunk hold consecutive
 // positions [P0, P0 + m) of the row's ascending candidate list, so the block
 // writes them to `cand`, keeps them in LDS and scores them right away.
-template <int kRrThreads>
+template <int kRrThreads, bool kFold>
 __global__ __launch_bounds__(kRrThreads) void compact_rerank_kernel(RetrieveArgs a) {
     constexpr int kKpt = kChunk / kRrThreads;   // keys per thread
     constexpr int kRrSlots = kRrThreads / 8;    // candidates reranked per block iteration
@@ -92,11 +203,15 @@ __global__ __launch_bounds__(kRrThreads) void compact_rerank_kernel(RetrieveArgs
     const int64_t grp = (int64_t)seq * a.hkv + hq / a.g;
 
     // Everything this block reads up front.
-    const int32_t* th = a.thresh + row * kThreshRow;
-    const uint32_t theta = (uint32_t)th[0];
-    const uint32_t quota = (uint32_t)th[2];
-    const int32_t* cb = a.chunk_base + (row * a.n_chunks + chunk) * 2;
-    const uint32_t base_g = (uint32_t)cb[0], base_e = (uint32_t)cb[1];
+    uint32_t theta = 0, quota = 0, base_g = 0, base_e = 0;
+    if constexpr (!kFold) {
+        const int32_t* th = a.thresh + row * kThreshRow;
+        const int32_t* cb = a.chunk_base + (row * a.n_chunks + chunk) * 2;
+        theta = (uint32_t)th[0];
+        quota = (uint32_t)th[2];
+        base_g = (uint32_t)cb[0];
+        base_e = (uint32_t)cb[1];
+    }
     // This thread's kKpt keys; score rows are padded to a multiple of 64 bytes, so a
     // load that starts before n stays inside the row.
     const int64_t i0 = chunk * kChunk + kKpt * tid;
@@ -133,6 +248,15 @@ __global__ __launch_bounds__(kRrThreads) void compact_rerank_kernel(RetrieveArgs
         }
     }
     if (tid < 16) s_tab[tid] = (tid & 8) ? -a.qc.a32[tid & 7] : a.qc.a32[tid & 7];
+
+    if constexpr (kFold) {
+        __shared__ FoldScratch<kRrThreads> s_fold;
+        const RowSelect r = row_select<kRrThreads>(a, row, chunk, s_fold);
+        theta = r.theta;
+        quota = r.quota;
+        base_g = r.base_g;
+        base_e = r.base_e;
+    }
 
     // ---- compaction: all S > theta, and S == theta while the row's quota lasts.
     uint32_t gmask = 0, emask = 0;
@@ -893,12 +1017,16 @@ hipError_t launch_compact_rerank(const RetrieveArgs& a, hipStream_t s) {
     const ProfEvents pe = prof_begin("compact_rerank");
     const dim3 grid((unsigned)a.n_chunks, (unsigned)(a.batch * a.hq));
     const int64_t blocks = (int64_t)grid.x * grid.y;
+#define PARISKV_RERANK(TH, FOLD) \
+    hipExtLaunchKernelGGL((compact_rerank_kernel<TH, FOLD>), grid, dim3(TH), 0, s, pe.start, pe.stop, 0, a)
+    const bool fold = fold_threshold(a);
     if (blocks <= kRrWidestGrid)
-        hipExtLaunchKernelGGL(compact_rerank_kernel<512>, grid, dim3(512), 0, s, pe.start, pe.stop, 0, a);
+        fold ? PARISKV_RERANK(512, true) : PARISKV_RERANK(512, false);
     else if (blocks <= kRrWideGrid)
-        hipExtLaunchKernelGGL(compact_rerank_kernel<256>, grid, dim3(256), 0, s, pe.start, pe.stop, 0, a);
+        fold ? PARISKV_RERANK(256, true) : PARISKV_RERANK(256, false);
     else
-        hipExtLaunchKernelGGL(compact_rerank_kernel<128>, grid, dim3(128), 0, s, pe.start, pe.stop, 0, a);
+        PARISKV_RERANK(128, false);
+#undef PARISKV_RERANK
     return hipGetLastError();
 }
 

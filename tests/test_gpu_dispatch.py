@@ -1,0 +1,70 @@
+"""GPU parity at the edges of the size rules that choose between forms of a kernel.  Every
+intermediate against the oracle, on one group where the shape is large."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2602_07721_amd as pk
+import workloads
+from parity import GpuRun, check_attention, check_head, check_index, oracle_group
+
+pytestmark = pytest.mark.gpu
+SCALE = 1.0 / np.sqrt(128.0)
+
+
+def _run(batch, hkv, G, n, bud, flags=0, seed=71):
+    """Retrieve on the GPU, two (sequence, KV head) groups checked in full; the run and its read-back."""
+    print(f"[dispatch] {batch} x {hkv} x {G}, n {n}, budget {bud}, flags {flags}", flush=True)
+    wc = workloads.Config("dispatch", batch=batch, n_kv_heads=hkv, q_per_kv=G, n=n, n_cand=bud[0], n_collide=bud[1],
+                          top_k=bud[2], seed=seed)
+    K, V = workloads.layer_kv(wc)
+    Q, _ = workloads.layer_queries(wc, K)
+    signs = workloads.rotation_signs(wc.seed)
+    budget = pk.Budget(*bud, flags=flags)
+    run = GpuRun(K, V, Q, signs, G, budget, SCALE, capacity=n + 5).retrieve()
+    inter = run.intermediates()
+    fused = run.retrieve_attend()
+    again = run.intermediates()
+    for name in ("cand", "cand_score", "idx", "score", "thresh"):
+        np.testing.assert_array_equal(inter[name].view(np.uint32), again[name].view(np.uint32))
+    np.testing.assert_array_equal(fused.view(np.uint32), run.attend(run.out_idx).view(np.uint32))
+    ids, rec, cnt = run.host_index()
+    for s, h in {(0, 0), (batch - 1, hkv - 1)}:
+        orc = oracle_group(K[s, h], signs)
+        check_index(ids[s, h], rec[s, h], cnt[s, h], orc)
+        for g in range(G):
+            check_head(inter, s, h, g, G, Q[s, h * G + g], orc, signs, budget, n)
+            check_attention(fused[s, h * G + g], Q[s, h * G + g], K[s, h], V[s, h], inter["idx"][s, h * G + g], SCALE)
+    return run, inter
+
+
+@pytest.mark.parametrize("batch,hkv,G,n,bud", [
+    # the scan reads a chunk in rounds of 2048 keys
+    (1, 1, 4, 2047, (200, 400, 30)), (1, 1, 3, 2049, (200, 400, 30)), (1, 2, 4, 4096 + 2048, (300, 600, 40)),
+    # 512 rerank blocks (512 threads each), 576 (256 threads), 2048 and 2080 (128 threads, threshold kernel)
+    (2, 8, 4, 8 * 4096 - 5, (700, 1400, 64)), (2, 8, 4, 8 * 4096 + 3, (700, 1400, 64)),
+    (16, 8, 4, 4 * 4096, (300, 600, 32)), (13, 8, 5, 3 * 4096 + 1, (300, 600, 32)),
+    # 32 chunks, the most whose threshold the rerank derives, and 33
+    (1, 1, 2, 32 * 4096, (2048, 4096, 100)), (1, 1, 2, 32 * 4096 + 1, (2048, 4096, 100)),
+])
+def test_chunk_and_grid_edges(batch, hkv, G, n, bud):
+    _run(batch, hkv, G, n, bud)
+
+
+@pytest.mark.parametrize("batch,hkv,G,n,bud", [(1, 1, 4, 2049, (200, 400, 30)), (1, 2, 4, 70001, (3000, 6000, 64)),
+                                               (2, 8, 4, 8 * 4096 + 3, (700, 1400, 64)), (1, 1, 1, 32 * 4096, (60000, 90000, 64))])
+def test_recount_in_the_rerank_equals_the_histogram(batch, hkv, G, n, bud):
+    _, inter = _run(batch, hkv, G, n, bud)
+    run, again = _run(batch, hkv, G, n, bud, flags=pk.EXACT_RECOUNT)
+    assert np.all(again["thresh"][..., 5] == 1)
+    for name in ("cand", "cand_score", "idx", "score"):
+        np.testing.assert_array_equal(inter[name].view(np.uint32), again[name].view(np.uint32))
+    # the per-chunk counts below each chunk, documented in the workspace layout
+    L = run.layout
+    base = run.ws[L["chunk_base"]:L["chunk_base"] + 8 * batch * hkv * G * L["n_chunks"]].cpu().numpy().view(np.int32)
+    base = base.reshape(batch, hkv * G, L["n_chunks"], 2)
+    for s, r in {(0, 0), (batch - 1, hkv * G - 1)}:
+        S, theta = again["S"][s, r, :n].astype(np.int64), again["thresh"][s, r, 0]
+        for c in range(L["n_chunks"]):
+            assert base[s, r, c, 0] == np.sum(S[:c * 4096] > theta) and base[s, r, c, 1] == np.sum(S[:c * 4096] == theta)
