@@ -1,5 +1,5 @@
 // Attention of one query head over a list of selected keys, for a block of
-// 1024 threads (Eqs. approx_weight, approx_output):
+// 1024 threads or, over short lists, fewer (Eqs. approx_weight, approx_output):
 //   o = sum_{i in list} softmax_i(scale <k_i, q>) v_i,  float16 in, float32 math.
 // Shared by the stand-alone attention kernel and the fused top-k + attention
 // kernel, so both produce the same bits.
@@ -11,6 +11,11 @@
 // per lane).  At the end the 4 slots of a wave merge by two butterfly steps
 // across its rows of 16 lanes (partners lane ^ 16, then lane ^ 32), and the 16
 // wave states merge through LDS, 8 threads per dimension.
+//
+// A block of 512 (256) threads plays the same 64 slots, 2 (4) per group of 16 lanes with 4 (2)
+// rows in flight each, over lists of at most 256 (128) rows, which is one round: every sum
+// is taken over the same values in the same order, so the result has the same bits.  Short
+// lists then cost a quarter of the waves, and several blocks share a CU.
 //
 // Rows come from one of two caches: a list entry with kWinRow set names row
 // (entry - kWinRow) of the window cache (Kw, Vw, win_capacity: Sink and Local /
@@ -31,9 +36,12 @@
 namespace pariskv {
 
 constexpr int kAtThreads = 1024;
-constexpr int kAtGroups = kAtThreads / 16;  // concurrent key slots per block
-constexpr int kAtWaves = kAtThreads / 64;   // slot states left after the in-wave merge
+constexpr int kAtGroups = kAtThreads / 16;  // key slots of a block
+constexpr int kAtWaves = kAtThreads / 64;   // slot states left after the merge of 4 slots
 constexpr int kAtUnroll = 8;                // K/V rows in flight per lane
+// Longest list a block of TH threads takes (one round of its rows in flight).
+template <int TH>
+constexpr int kAtRows = TH == kAtThreads ? kMaxAttendRows : kAtGroups * kAtUnroll * TH / kAtThreads;
 
 // LDS the row needs beyond the key list: running max, sum and accumulators per wave.
 struct AttendScratch {
@@ -73,16 +81,21 @@ __device__ __forceinline__ uint4 attend_query_part(const __half* q_row) {
 
 // qv: this thread's query part (attend_query_part); K, V: the KV head's rows
 // [kv_capacity][D]; Kw, Vw: its window-cache rows [win_capacity][D] (entries
-// with kWinRow); list: k entries in LDS (already synchronised); out: D floats.
+// with kWinRow); list: k <= kAtRows<TH> entries in LDS (already synchronised); out: D floats.
 // Every thread of the block must call it; it ends with the block synchronised.
+template <int TH = kAtThreads>
 __device__ __forceinline__ void attend_row(uint4 qv, const __half* __restrict__ K,
                                            const __half* __restrict__ V, int64_t kv_capacity,
                                            const __half* __restrict__ Kw, const __half* __restrict__ Vw,
                                            int64_t win_capacity, const int32_t* list, int32_t k,
                                            float scale, float* __restrict__ out, AttendScratch& sm,
                                            const uint4* prow = nullptr) {
+    constexpr int kSlots = kAtThreads / TH;       // slots a group of 16 lanes plays
+    constexpr int kRows = kAtUnroll / kSlots;     // rows in flight per slot
+    constexpr int kGroups = kAtGroups / kSlots;   // groups of 16 lanes in the block
+    constexpr int kWaves = TH / 64;
     const int tid = threadIdx.x;
-    const int grp16 = tid >> 4;  // key slot 0 .. kAtGroups-1
+    const int grp16 = tid >> 4;  // key slots grp16, grp16 + kGroups, ...
     const int l16 = tid & 15;
 
     float qf[8];
@@ -90,124 +103,140 @@ __device__ __forceinline__ void attend_row(uint4 qv, const __half* __restrict__ 
 #pragma unroll
     for (int d = 0; d < 8; ++d) qf[d] *= scale;
 
-    float m = -__builtin_huge_valf(), lsum = 0.f;
-    float acc[8];
+    float m[kSlots], lsum[kSlots], acc[kSlots][8];
 #pragma unroll
-    for (int d = 0; d < 8; ++d) acc[d] = 0.f;
+    for (int v = 0; v < kSlots; ++v) {
+        m[v] = -__builtin_huge_valf();
+        lsum[v] = 0.f;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) acc[v][d] = 0.f;
+    }
 
-    for (int base = 0; base < k; base += kAtGroups * kAtUnroll) {
-        int32_t key[kAtUnroll];
+    for (int base = 0; base < k; base += kAtGroups * kRows) {
+        int32_t key[kAtUnroll];  // row u of slot v at v kRows + u
         uint4 kc[kAtUnroll], vc[kAtUnroll];
 #pragma unroll
-        for (int u = 0; u < kAtUnroll; ++u) {
-            const int r = base + grp16 + kAtGroups * u;
-            key[u] = r < k ? list[r] : -1;
-            const bool win = key[u] >= kWinRow;
-            const int64_t rowi = win ? key[u] - kWinRow : key[u];
-            if (rowi >= (win ? win_capacity : kv_capacity)) key[u] = -1;
-            kc[u] = make_uint4(0, 0, 0, 0);
-            vc[u] = make_uint4(0, 0, 0, 0);
+        for (int i = 0; i < kAtUnroll; ++i) {
+            const int r = base + grp16 + kGroups * (i / kRows) + kAtGroups * (i % kRows);
+            key[i] = r < k ? list[r] : -1;
+            const bool win = key[i] >= kWinRow;
+            const int64_t rowi = win ? key[i] - kWinRow : key[i];
+            if (rowi >= (win ? win_capacity : kv_capacity)) key[i] = -1;
+            kc[i] = make_uint4(0, 0, 0, 0);
+            vc[i] = make_uint4(0, 0, 0, 0);
             // A held row (entry <= -2 with prow) is read from LDS where it is used.
-            if (prow == nullptr && key[u] < 0) key[u] = -1;
-            if (key[u] >= 0) {
+            if (prow == nullptr && key[i] < 0) key[i] = -1;
+            if (key[i] >= 0) {
                 const int64_t off = rowi * kD;
-                kc[u] = reinterpret_cast<const uint4*>((win ? Kw : K) + off)[l16];
-                vc[u] = reinterpret_cast<const uint4*>((win ? Vw : V) + off)[l16];
+                kc[i] = reinterpret_cast<const uint4*>((win ? Kw : K) + off)[l16];
+                vc[i] = reinterpret_cast<const uint4*>((win ? Vw : V) + off)[l16];
             }
         }
         float dot[kAtUnroll];
 #pragma unroll
-        for (int u = 0; u < kAtUnroll; ++u) {
-            if (prow != nullptr && key[u] <= -2) {
-                kc[u] = prow[32 * (-2 - key[u]) + l16];
-                vc[u] = prow[32 * (-2 - key[u]) + 16 + l16];
+        for (int i = 0; i < kAtUnroll; ++i) {
+            if (prow != nullptr && key[i] <= -2) {
+                kc[i] = prow[32 * (-2 - key[i]) + l16];
+                vc[i] = prow[32 * (-2 - key[i]) + 16 + l16];
             }
             float kf[8];
-            unpack8_half(kc[u], kf);
+            unpack8_half(kc[i], kf);
             float d0 = 0.f;
 #pragma unroll
             for (int d = 0; d < 8; ++d) d0 += qf[d] * kf[d];
-            dot[u] = d0;
+            dot[i] = d0;
         }
 #pragma unroll
-        for (int u = 0; u < kAtUnroll; ++u) dot[u] = sum16(dot[u]);
-        float mn = m;
+        for (int i = 0; i < kAtUnroll; ++i) dot[i] = sum16(dot[i]);
 #pragma unroll
-        for (int u = 0; u < kAtUnroll; ++u)
-            if (key[u] != -1) mn = fmaxf(mn, dot[u]);
-        if (mn > -__builtin_huge_valf()) {
-            const float corr = __expf(m - mn);
-            lsum *= corr;
+        for (int v = 0; v < kSlots; ++v) {
+            float mn = m[v];
 #pragma unroll
-            for (int d = 0; d < 8; ++d) acc[d] *= corr;
+            for (int u = 0; u < kRows; ++u)
+                if (key[v * kRows + u] != -1) mn = fmaxf(mn, dot[v * kRows + u]);
+            if (mn > -__builtin_huge_valf()) {
+                const float corr = __expf(m[v] - mn);
+                lsum[v] *= corr;
 #pragma unroll
-            for (int u = 0; u < kAtUnroll; ++u) {
-                if (key[u] != -1) {
-                    const float p = __expf(dot[u] - mn);
-                    float vf[8];
-                    unpack8_half(vc[u], vf);
-                    lsum += p;
+                for (int d = 0; d < 8; ++d) acc[v][d] *= corr;
 #pragma unroll
-                    for (int d = 0; d < 8; ++d) acc[d] += p * vf[d];
+                for (int u = 0; u < kRows; ++u) {
+                    const int i = v * kRows + u;
+                    if (key[i] != -1) {
+                        const float p = __expf(dot[i] - mn);
+                        float vf[8];
+                        unpack8_half(vc[i], vf);
+                        lsum[v] += p;
+#pragma unroll
+                        for (int d = 0; d < 8; ++d) acc[v][d] += p * vf[d];
+                    }
                 }
+                m[v] = mn;
             }
-            m = mn;
         }
     }
 
-    // The wave's 4 slot states (rows of 16 lanes holding the same dims) into one.
+    // The 4 slots in the rows of 16 lanes of a wave (holding the same dims) into one.
     const int lane = tid & 63;
-#pragma unroll
-    for (int step = 16; step <= 32; step <<= 1) {
-        const float mp = __uint_as_float(lane_xor(__float_as_uint(m), step, lane));
-        const float lp = __uint_as_float(lane_xor(__float_as_uint(lsum), step, lane));
-        float ap[8];
-#pragma unroll
-        for (int d = 0; d < 8; ++d) ap[d] = __uint_as_float(lane_xor(__float_as_uint(acc[d]), step, lane));
-        const float mn = fmaxf(m, mp);
-        if (mn > -__builtin_huge_valf()) {
-            const float c0 = __expf(m - mn), c1 = __expf(mp - mn);
-            lsum = lsum * c0 + lp * c1;
-#pragma unroll
-            for (int d = 0; d < 8; ++d) acc[d] = acc[d] * c0 + ap[d] * c1;
-        }
-        m = mn;
-    }
     const int wave = tid >> 6;
-    if (lane < 16) {
-        if (l16 == 0) {
-            sm.m[wave] = m;
-            sm.l[wave] = lsum;
-        }
 #pragma unroll
-        for (int d = 0; d < 8; ++d) sm.acc[wave][8 * l16 + d] = acc[d];
+    for (int v = 0; v < kSlots; ++v) {
+#pragma unroll
+        for (int step = 16; step <= 32; step <<= 1) {
+            const float mp = __uint_as_float(lane_xor(__float_as_uint(m[v]), step, lane));
+            const float lp = __uint_as_float(lane_xor(__float_as_uint(lsum[v]), step, lane));
+            float ap[8];
+#pragma unroll
+            for (int d = 0; d < 8; ++d) ap[d] = __uint_as_float(lane_xor(__float_as_uint(acc[v][d]), step, lane));
+            const float mn = fmaxf(m[v], mp);
+            if (mn > -__builtin_huge_valf()) {
+                const float c0 = __expf(m[v] - mn), c1 = __expf(mp - mn);
+                lsum[v] = lsum[v] * c0 + lp * c1;
+#pragma unroll
+                for (int d = 0; d < 8; ++d) acc[v][d] = acc[v][d] * c0 + ap[d] * c1;
+            }
+            m[v] = mn;
+        }
+        if (lane < 16) {
+            const int st = wave + kWaves * v;  // slots 4 st .. 4 st + 3
+            if (l16 == 0) {
+                sm.m[st] = m[v];
+                sm.l[st] = lsum[v];
+            }
+#pragma unroll
+            for (int d = 0; d < 8; ++d) sm.acc[st][8 * l16 + d] = acc[v][d];
+        }
     }
     __syncthreads();
     {
-        // Every thread: dim d of 2 of the 16 wave states, then a sum over the 8 threads
+        // Every thread: dim d of 2 of the 16 states, then a sum over the 8 threads
         // of the dim (lanes 8 d' + part) by lane exchanges.  An empty state (m = -inf,
         // l = 0, acc = 0) is scaled by exp(-inf) = 0, so it needs no test.
         static_assert(kAtThreads == 8 * kD && kAtWaves == 16, "8 threads per dim, 2 states each");
-        const int d = tid >> 3, part = tid & 7;
         float M = -__builtin_huge_valf();
 #pragma unroll
         for (int j = 0; j < kAtWaves; ++j) M = fmaxf(M, sm.m[j]);
-        float L = 0.f, O = 0.f;
-        if (M > -__builtin_huge_valf()) {
+        const int part = tid & 7;
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int j = 2 * part + r;
-                const float c = __expf(sm.m[j] - M);
-                L += sm.l[j] * c;
-                O += sm.acc[j][d] * c;
+        for (int v = 0; v < kSlots; ++v) {
+            const int d = (tid >> 3) + TH / 8 * v;
+            float L = 0.f, O = 0.f;
+            if (M > -__builtin_huge_valf()) {
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const int j = 2 * part + r;
+                    const float c = __expf(sm.m[j] - M);
+                    L += sm.l[j] * c;
+                    O += sm.acc[j][d] * c;
+                }
             }
-        }
 #pragma unroll
-        for (int x = 1; x < 8; x <<= 1) {
-            L += __uint_as_float(lane_xor(__float_as_uint(L), x, lane));
-            O += __uint_as_float(lane_xor(__float_as_uint(O), x, lane));
+            for (int x = 1; x < 8; x <<= 1) {
+                L += __uint_as_float(lane_xor(__float_as_uint(L), x, lane));
+                O += __uint_as_float(lane_xor(__float_as_uint(O), x, lane));
+            }
+            if (part == 0) out[d] = L > 0.f ? O / L : 0.f;
         }
-        if (part == 0) out[d] = L > 0.f ? O / L : 0.f;
     }
     __syncthreads();
 }

@@ -24,8 +24,8 @@
 // keeps the 16 query coordinates of its two subspaces in registers; the
 // signed level table (16 floats) lives in LDS.
 //
-// topk_reg_kernel (at most 8 candidates per thread) and topk_lds_kernel (more):
-// one block per list; the k-th largest estimate is found exactly on
+// topk_reg_kernel (blocks of 256, 512 or 1024 threads, at most 8 candidates per thread) and
+// topk_lds_kernel (more): one block per list; the k-th largest estimate is found exactly on
 // order-preserving uint32 keys, ties at it taken in candidate order, then an
 // ordered compaction lists the winners in ascending key index (candidate order)
 // without a sort.  The keys are held in registers (staged in LDS by the second
@@ -55,6 +55,7 @@ constexpr int64_t kRrWidestGrid = 512;
 static_assert(kTopkPart >= PARISKV_MAX_TOPK, "a top-k slice holds at least k candidates");
 static_assert(PARISKV_MAX_CAND / kTopkPart * PARISKV_MAX_TOPK <= 1024 * 32, "the slices' winners fit one block");
 constexpr int kRrUnroll = 4;  // records in flight per lane
+constexpr int64_t kManyRows = 256;  // top-k blocks past one per CU
 
 // Order-preserving uint32 key of a float (larger float, larger key; finite floats
 // map above 0) and back.
@@ -664,12 +665,14 @@ template <int TH, int EPT, bool kAttend>
 __global__ __launch_bounds__(TH) void topk_reg_kernel(RetrieveArgs a) {
     constexpr int kWaves = TH / 64;
     constexpr int kIt = EPT / 4;   // 4-candidate groups per thread
-    constexpr int kNB = 2048;
+    constexpr int kNB = 2 * TH;    // bins of the histogram
+    constexpr int kDigit = TH == 1024 ? 11 : TH == 512 ? 10 : 9;  // log2 kNB
+    static_assert(kNB == 1 << kDigit, "digit width");
     // LDS: region A = the attention's per-slot state (kAttend), region B = two
     // histograms, whose place the attention list takes once they are done.
     constexpr size_t kA = kAttend ? sizeof(AttendScratch) : 0;
     constexpr size_t kBytes = kA + 2 * kNB * 4;
-    static_assert(!kAttend || 2 * kNB * 4 >= kMaxAttendRows * 4, "the attention list fits in region B");
+    static_assert(!kAttend || 2 * kNB >= kAtRows<TH>, "the attention list fits in region B");
     static_assert(EPT % 4 == 0 && EPT <= 8, "whole 4-candidate groups, few enough to stay in registers");
     __shared__ __align__(16) unsigned char s_raw[kBytes];
     uint32_t (*s_hist)[kNB] = reinterpret_cast<uint32_t (*)[kNB]>(s_raw + kA);
@@ -679,7 +682,7 @@ __global__ __launch_bounds__(TH) void topk_reg_kernel(RetrieveArgs a) {
     __shared__ uint32_t s_digit, s_need, s_nsmall;
     __shared__ uint32_t s_small[64];
     // With kAttend the winners' estimates wait here until the attention is done.
-    __shared__ float s_wsc[kAttend ? PARISKV_MAX_TOPK : 1];
+    __shared__ float s_wsc[kAttend ? (kAtRows<TH> < PARISKV_MAX_TOPK ? kAtRows<TH> : PARISKV_MAX_TOPK) : 1];
     __shared__ int32_t s_dump[kAttend ? TH : 1];  // a word per thread for non-winners' stores
     // With kAttend: K/V rows of up to kPf sure winners per wave, requested as soon as
     // the boundary bin is known (see below), and their cache rows.
@@ -759,7 +762,7 @@ __global__ __launch_bounds__(TH) void topk_reg_kernel(RetrieveArgs a) {
         kmax = max(kmax, s_mm[1][w]);
     }
 
-    // Pass 0: 2048 bins linear in the score over [min, max].  The float bit
+    // Pass 0: kNB bins linear in the score over [min, max].  The float bit
     // patterns of the scores are concentrated in few sign/exponent prefixes, so
     // value-linear bins spread the counts (and the atomics) far better.  The bin
     // index is a non-decreasing function of the score, so the keys of a higher
@@ -850,11 +853,12 @@ __global__ __launch_bounds__(TH) void topk_reg_kernel(RetrieveArgs a) {
         T = (uint32_t)__builtin_amdgcn_readlane((int)kl, first);
         quota = need - (uint32_t)__builtin_amdgcn_readlane((int)gt, first);
     } else {
-        // Exact radix select on the full key restricted to the bin: 11, 11, 10 bits.
+        // Exact radix select on the full key restricted to the bin: kDigit bits a pass (the
+        // last one repeats bits that are already fixed).
         uint32_t prefix = 0, mask = 0;
-        int shift = 21;
+        int shift = 32 - kDigit;
 #pragma unroll 1
-        for (int pass = 1; pass <= 3; ++pass) {
+        for (int pass = 1; pass <= (32 + kDigit - 1) / kDigit; ++pass) {
             uint32_t* hist = s_hist[pass & 1];
 #pragma unroll
             for (int e = 0; e < EPT; ++e)
@@ -868,7 +872,7 @@ __global__ __launch_bounds__(TH) void topk_reg_kernel(RetrieveArgs a) {
             prefix |= s_digit << shift;
             mask |= (uint32_t)(kNB - 1) << shift;
             need = s_need;
-            shift = shift >= 11 ? shift - 11 : 0;
+            shift = shift >= kDigit ? shift - kDigit : 0;
         }
         T = prefix;     // the kk-th largest key value
         quota = need;   // how many keys equal to T are taken (lowest indices)
@@ -902,9 +906,9 @@ __global__ __launch_bounds__(TH) void topk_reg_kernel(RetrieveArgs a) {
         pre[it] = incl - mine;
     }
     __syncthreads();
-    // The waves' totals of each group: lane w < 16 takes wave w's, one wave scan, and
-    // the prefix before this wave read from lane wave - 1 (the group total from 15).
-    static_assert(kWaves == 16, "one lane per wave in the scan of the wave totals");
+    // The waves' totals of each group: lane w < kWaves takes wave w's, one wave scan, and
+    // the prefix before this wave read from lane wave - 1 (the group total from the last).
+    static_assert(kWaves <= 64, "one lane per wave in the scan of the wave totals");
     uint32_t before_groups = 0;
 #pragma unroll
     for (int it = 0; it < kIt; ++it) {
@@ -982,7 +986,7 @@ __global__ __launch_bounds__(TH) void topk_reg_kernel(RetrieveArgs a) {
         __syncthreads();
         const bool wc = a.win.win_capacity > 0;
         const int64_t wrow0 = wc ? (int64_t)((int)row / a.g) * a.win.win_capacity : kvrow0;
-        attend_row(qv, static_cast<const __half*>(a.K) + kvrow0 * kD,
+        attend_row<TH>(qv, static_cast<const __half*>(a.K) + kvrow0 * kD,
                    static_cast<const __half*>(a.V) + kvrow0 * kD, a.kv_capacity,
                    static_cast<const __half*>(wc ? a.Kw : a.K) + wrow0 * kD,
                    static_cast<const __half*>(wc ? a.Vw : a.V) + wrow0 * kD, a.win.win_capacity,
@@ -1068,20 +1072,36 @@ hipError_t launch_topk(const RetrieveArgs& a0, hipStream_t s, bool attend, bool*
     const int64_t C = a.tk_c;
     if (fused) *fused = attend;
     const ProfEvents pe = prof_begin(attend ? "topk_attend" : "topk");
-#define PARISKV_TOPK_REG(EPT)                                                                        \
-    (attend ? hipExtLaunchKernelGGL((topk_reg_kernel<1024, EPT, true>), grid, dim3(1024), 0, s,       \
+#define PARISKV_TOPK_REG(TH, EPT)                                                                    \
+    (attend ? hipExtLaunchKernelGGL((topk_reg_kernel<TH, EPT, true>), grid, dim3(TH), 0, s,           \
                                     pe.start, pe.stop, 0, a)                                          \
-            : hipExtLaunchKernelGGL((topk_reg_kernel<1024, EPT, false>), grid, dim3(1024), 0, s,      \
+            : hipExtLaunchKernelGGL((topk_reg_kernel<TH, EPT, false>), grid, dim3(TH), 0, s,          \
                                     pe.start, pe.stop, 0, a))
 #define PARISKV_TOPK_LDS(EPT)                                                                        \
     (attend ? hipExtLaunchKernelGGL((topk_lds_kernel<1024, EPT, true>), grid, dim3(1024), 0, s,       \
                                     pe.start, pe.stop, 0, a)                                          \
             : hipExtLaunchKernelGGL((topk_lds_kernel<1024, EPT, false>), grid, dim3(1024), 0, s,      \
                                     pe.start, pe.stop, 0, a))
-    if (C <= 1024 * 4)
-        PARISKV_TOPK_REG(4);
+    // The smallest block that holds the candidates in registers and the attended list in one
+    // round, at 4 candidates per thread: fewer waves at every barrier, and 2 to 4 blocks a CU
+    // where there are more rows than CUs (448 rows, C = 876, k = 100: 19.8 -> 11.1 us; 8 rows,
+    // C = 512, k = 64: 9.9 -> 9.1).  8 per thread instead of twice the threads pays only with
+    // more rows than CUs (512 rows, C = 2048, k = 256: 23.7 -> 17.3 us; 128 rows, C = 2855,
+    // k = 256: 12.1 -> 12.7).
+    const int64_t list = attend ? a.win.dense_rows() + a.top_k : 0;  // rows attended
+    const int64_t per = rows > kManyRows ? 8 : 4;
+    if (C <= 256 * 4 && list <= kAtRows<256>)
+        PARISKV_TOPK_REG(256, 4);
+    else if (C <= 256 * per && list <= kAtRows<256>)
+        PARISKV_TOPK_REG(256, 8);
+    else if (C <= 512 * 4 && list <= kAtRows<512>)
+        PARISKV_TOPK_REG(512, 4);
+    else if (C <= 512 * per && list <= kAtRows<512>)
+        PARISKV_TOPK_REG(512, 8);
+    else if (C <= 1024 * 4)
+        PARISKV_TOPK_REG(1024, 4);
     else if (C <= 1024 * 8)
-        PARISKV_TOPK_REG(8);
+        PARISKV_TOPK_REG(1024, 8);
     else if (C <= 1024 * 16)
         PARISKV_TOPK_LDS(16);
     else

@@ -68,3 +68,34 @@ def test_recount_in_the_rerank_equals_the_histogram(batch, hkv, G, n, bud):
         S, theta = again["S"][s, r, :n].astype(np.int64), again["thresh"][s, r, 0]
         for c in range(L["n_chunks"]):
             assert base[s, r, c, 0] == np.sum(S[:c * 4096] > theta) and base[s, r, c, 1] == np.sum(S[:c * 4096] == theta)
+
+
+@pytest.mark.parametrize("batch,hkv,G,n,bud", [
+    # top-k blocks of 256, 512 and 1024 threads: 1024 / 1025, 2048 / 2049 and 4096 / 4097
+    # candidates, lists of 128 / 129 and 256 / 257 rows
+    (1, 1, 3, 3000, (1024, 2048, 128)), (1, 1, 3, 3000, (1024, 2048, 129)), (1, 1, 3, 3000, (1025, 2048, 128)),
+    (1, 1, 2, 6000, (2048, 4096, 256)), (1, 1, 2, 6000, (2048, 4096, 257)), (1, 1, 2, 6000, (2049, 4096, 1)),
+    # more than 256 rows: 8 candidates per thread
+    (17, 4, 4, 2500, (2048, 4096, 128)), (17, 4, 4, 2500, (2049, 4096, 128)), (17, 4, 4, 4200, (4096, 6000, 256)),
+    (17, 4, 4, 4200, (4097, 6000, 200)), (17, 4, 4, 1100, (1024, 2000, 5)),
+])
+def test_top_k_block_edges(batch, hkv, G, n, bud):
+    _run(batch, hkv, G, n, bud)
+
+
+@pytest.mark.parametrize("batch,C,k", [(1, 700, 50), (1, 2000, 200), (9, 2000, 100), (9, 4000, 200)])
+def test_equal_estimates_take_the_radix_passes(batch, C, k):
+    # a zero query: every estimate is 0, so the boundary bin holds all of them
+    n, hkv, G = 5000, 8, 4
+    wc = workloads.Config("zero", batch=batch, n_kv_heads=hkv, q_per_kv=G, n=n, n_cand=C, n_collide=2 * C, top_k=k, seed=72)
+    K, V = workloads.layer_kv(wc)
+    Q, _ = workloads.layer_queries(wc, K)
+    Q[:, ::3] = 0
+    run = GpuRun(K, V, Q, workloads.rotation_signs(72), G, pk.Budget(C, 2 * C, k), SCALE).retrieve()
+    inter = run.intermediates()
+    np.testing.assert_array_equal(run.retrieve_attend().view(np.uint32), run.attend(run.out_idx).view(np.uint32))
+    for s in range(batch):
+        for h in range(hkv * G):
+            c, e = inter["cand"][s, h], inter["cand_score"][s, h]
+            np.testing.assert_array_equal(inter["idx"][s, h], np.sort(c[np.lexsort((c, -e))[:k]]))
+            assert h % 3 or not e.any()
