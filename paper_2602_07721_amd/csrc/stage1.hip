@@ -5,8 +5,8 @@
 // "Top-beta selection with small-range integer scores"; Alg. 1 Stage I).
 //
 // Kernels, in launch order:
-//   query_lut_kernel   one block per (sequence, KV head, quad, 4 subspaces), one
-//                      wave per (head slot, subspace): z = H(s q) in exact
+//   query_lut_kernel   one block per (sequence, KV head, quad, 4 subspaces; few
+//                      quads: 1 subspace), one wave per (head slot, subspace): z = H(s q) in exact
 //                      float64 by a register FWHT in one wave per head
 //                      (written as z/D float for the rerank), the 256
 //                      centroids ranked by the exact proxy sum_j +-z_j (ties:
@@ -139,33 +139,41 @@ __device__ __forceinline__ uint32_t hist_floor(const float* st, int64_t n, int64
 
 // ---------------------------------------------------------------- query + LUT
 
-constexpr int kLutThreads = 1024;  // 16 waves: 4 head slots x 4 subspaces
+// Up to this many quads of query heads the 16 subspaces of a quad go to 16 blocks of 4 waves,
+// each wave taking its own head's transform: the rankings spread over four times the CUs, one
+// wave to a SIMD.  8 quads (32 heads x 32K keys) 31.8 -> 30.1 us a call, 32 quads (128 heads x
+// 45K) 45.9 -> 44.4.  From 64 quads on, blocks of 4 subspaces that share the transforms already
+// fill the chip (64 quads of 128K keys 128.2 -> 128.5 with 16 blocks).
+constexpr int64_t kLutNarrow = 32;
 
-__global__ __launch_bounds__(kLutThreads) void query_lut_kernel(RetrieveArgs a) {
+// kSubs: subspaces per block, one wave per (head slot, subspace).
+template <int kSubs>
+__global__ __launch_bounds__(256 * kSubs) void query_lut_kernel(RetrieveArgs a) {
+    constexpr int kGroups = kB / kSubs;            // blocks per quad
     __shared__ double s_z[4][kD];
-    __shared__ uint32_t s_cnt[4][kCentroids];
-    __shared__ uint32_t s_lut[4][kCentroids];  // packed bonus words of the 4 subspaces
+    __shared__ uint32_t s_cnt[kSubs][kCentroids];
+    __shared__ uint32_t s_lut[kSubs][kCentroids];  // packed bonus words of the block's subspaces
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    const int slot = wave >> 2;          // head of the quad
-    const int sub = wave & 3;
+    const int slot = wave / kSubs;       // head of the quad
+    const int sub = wave % kSubs;
 
-    // blockIdx.x = ((seq * hkv + kvh) * quads + quad) * 4 + subspace group
-    const int sg = blockIdx.x & 3;
-    const int64_t gq = blockIdx.x >> 2;  // (seq * hkv + kvh) * quads + quad
+    // blockIdx.x = ((seq * hkv + kvh) * quads + quad) * kGroups + subspace group
+    const int sg = blockIdx.x % kGroups;
+    const int64_t gq = blockIdx.x / kGroups;  // (seq * hkv + kvh) * quads + quad
     const int quad = (int)(gq % a.quads);
     const int64_t grp = gq / a.quads;    // seq * hkv + kvh
     const int seq = (int)(grp / a.hkv);
     const int kvh = (int)(grp % a.hkv);
-    const int b = 4 * sg + sub;          // this wave's subspace
+    const int b = kSubs * sg + sub;      // this wave's subspace
     const int hg = quad * 4 + slot;      // head within the KV group
     const bool live = hg < a.g;
     const int64_t row = (int64_t)seq * a.hq + kvh * a.g + hg;
 
     // Cluster counts of the 4 subspaces, requested first and put in LDS after the
     // transform; the sign word of this lane's coordinates picked without indexing.
-    const uint32_t* cnt = a.counts + grp * (kB * kCentroids) + (4 * sg) * kCentroids;
+    const uint32_t* cnt = a.counts + grp * (kB * kCentroids) + (kSubs * sg) * kCentroids;
     const uint32_t cval = cnt[tid];
     const uint32_t sword = select_mask(0xFFFFFFFF00000000ull,
                                        select_mask(0xFFFF0000FFFF0000ull, a.sb.w[3], a.sb.w[2]),
@@ -177,7 +185,7 @@ __global__ __launch_bounds__(kLutThreads) void query_lut_kernel(RetrieveArgs a) 
     // waves.  Waves w = 4 slot + sub go to SIMD w mod 4, so the 4 transforms run on 4
     // different SIMDs.
     const bool rotate = !(a.flags & kFlagNoRotation);
-    if (sub == slot && live) {
+    if (sub == slot % kSubs && live) {
         const uint32_t qw = reinterpret_cast<const uint32_t*>(static_cast<const __half*>(a.q) + row * kD)[lane];
         double z[2];
 #pragma unroll
@@ -290,7 +298,7 @@ __global__ __launch_bounds__(kLutThreads) void query_lut_kernel(RetrieveArgs a) 
     }
     __syncthreads();
     // Unused slots of the last quad keep bonus 0.
-    a.lut[gq * (kB * kCentroids) + (4 * sg) * kCentroids + tid] = (&s_lut[0][0])[tid];
+    a.lut[gq * (kB * kCentroids) + (kSubs * sg) * kCentroids + tid] = (&s_lut[0][0])[tid];
 }
 
 // ---------------------------------------------------------------- collision scan
@@ -657,9 +665,12 @@ __global__ __launch_bounds__(kThrThreads) void threshold_kernel(RetrieveArgs a) 
 }  // namespace
 
 hipError_t launch_query_lut(const RetrieveArgs& a, hipStream_t s) {
-    const int64_t blocks = (int64_t)a.batch * a.hkv * a.quads * 4;
+    const int64_t quads = (int64_t)a.batch * a.hkv * a.quads;
     const ProfEvents pe = prof_begin("query_lut");
-    hipExtLaunchKernelGGL(query_lut_kernel, dim3((unsigned)blocks), dim3(kLutThreads), 0, s, pe.start, pe.stop, 0, a);
+    if (quads <= kLutNarrow)
+        hipExtLaunchKernelGGL(query_lut_kernel<1>, dim3((unsigned)(quads * 16)), dim3(256), 0, s, pe.start, pe.stop, 0, a);
+    else
+        hipExtLaunchKernelGGL(query_lut_kernel<4>, dim3((unsigned)(quads * 4)), dim3(1024), 0, s, pe.start, pe.stop, 0, a);
     return hipGetLastError();
 }
 

@@ -83,6 +83,12 @@ def test_top_k_block_edges(batch, hkv, G, n, bud):
     _run(batch, hkv, G, n, bud)
 
 
+@pytest.mark.parametrize("batch,hkv,G", [(4, 8, 4), (11, 3, 4), (4, 4, 8), (11, 1, 10), (3, 11, 1)])
+def test_query_block_edges(batch, hkv, G):
+    # 32 and 33 quads of query heads: 1 and 4 subspaces per block; partial quads
+    _run(batch, hkv, G, 1500, (200, 400, 20))
+
+
 @pytest.mark.parametrize("batch,C,k", [(1, 700, 50), (1, 2000, 200), (9, 2000, 100), (9, 4000, 200)])
 def test_equal_estimates_take_the_radix_passes(batch, C, k):
     # a zero query: every estimate is 0, so the boundary bin holds all of them
