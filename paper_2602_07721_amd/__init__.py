@@ -78,6 +78,16 @@ class _Layout(ctypes.Structure):
 
 
 _lib = None
+_torch_module = None
+
+
+def _torch():
+    """torch, imported at the first call that takes tensors."""
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def lib():
@@ -181,59 +191,72 @@ class Budget:
 def _ptr(t, name, device=True):
     if t is None:
         return None
-    import torch
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _torch().Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if device and not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _torch()
+    if torch.cuda.is_initialized():
+        # torch.cuda.current_stream().cuda_stream without the Stream object (3 us of a small call).
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _arg(t, name, dtype, shape, dev=None, optional=False):
     """Pointer of a tensor argument after checking its dtype and its shape (None entries are
     free; the sizes the library derives from shapes must be consistent).  The kernels trust
     these, so a mismatch is refused here rather than read past the end of an allocation.
-    A tensor that must live on the GPU is appended to the list `dev`, checked by
+    A tensor that must live on the GPU and does not is appended to the list `dev`, refused by
     _require_device once every argument of the call has passed these checks."""
-    import torch
+    if isinstance(t, _torch().Tensor) and t.dtype == dtype and t.shape == shape:
+        # The whole shape given and equal: the ordinary case, in one comparison.
+        if dev is not None and not t.is_cuda:
+            dev.append((t, name))
+        if t.is_contiguous():
+            return t.data_ptr()
     if t is None:
         if optional:
             return None
         raise ValueError(f"{name} is required")
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _torch().Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if t.dim() != len(shape) or any(w is not None and int(d) != int(w) for d, w in zip(t.shape, shape)):
         want = "[" + ", ".join("*" if w is None else str(w) for w in shape) + "]"
         raise ValueError(f"{name} must have shape {want}, got {list(t.shape)}")
-    if dev is not None:
+    if dev is not None and not t.is_cuda:
         dev.append((t, name))
     return _ptr(t, name, False)
 
 
 def _require_device(dev):
-    for t, name in dev:
-        if not t.is_cuda:
-            raise ValueError(f"{name} must be a GPU tensor")
+    for _, name in dev:
+        raise ValueError(f"{name} must be a GPU tensor")
+
+
+def _rows(t):
+    """The third dimension of a [batch][Hkv][rows][D] tensor (None, which is any, for what is not one)."""
+    return t.shape[2] if isinstance(t, _torch().Tensor) and t.dim() == 4 else None
 
 
 def _kv_args(cfg, batch, K, V, kv_host_mapped, dev, names=("K", "V")):
     """Pointers of a K/V cache pair [batch][Hkv][capacity][D] float16 (pinned host memory when
     kv_host_mapped) and its capacity."""
-    import torch
-    shape = (batch, cfg.n_kv_heads, None, HEAD_DIM)
-    kp = _arg(K, names[0], torch.float16, shape, None if kv_host_mapped else dev)
-    cap = int(K.shape[2])
-    vp = _arg(V, names[1], torch.float16, (batch, cfg.n_kv_heads, cap, HEAD_DIM), None if kv_host_mapped else dev)
+    half = _torch().float16
+    if kv_host_mapped:
+        dev = None
+    kp = _arg(K, names[0], half, (batch, cfg.n_kv_heads, _rows(K), HEAD_DIM), dev)
+    cap = K.shape[2]
+    vp = _arg(V, names[1], half, (batch, cfg.n_kv_heads, cap, HEAD_DIM), dev)
     if kv_host_mapped:
         for t, nm in ((K, names[0]), (V, names[1])):
             if t.is_cuda or not t.is_pinned():
@@ -242,22 +265,22 @@ def _kv_args(cfg, batch, K, V, kv_host_mapped, dev, names=("K", "V")):
 
 
 def _q_arg(cfg, q, dev):
-    import torch
+    torch = _torch()
     if not isinstance(q, torch.Tensor) or q.dim() != 3:
         raise ValueError("q must be a [batch][Hq][D] tensor")
-    batch = int(q.shape[0])
+    batch = q.shape[0]
     return _arg(q, "q", torch.float16, (batch, cfg.n_q_heads, HEAD_DIM), dev), batch
 
 
 def _out_arg(cfg, out, batch, device, dev):
-    import torch
+    torch = _torch()
     if out is None:
         out = torch.empty((batch, cfg.n_q_heads, HEAD_DIM), dtype=torch.float32, device=device)
     return out, _arg(out, "out", torch.float32, (batch, cfg.n_q_heads, HEAD_DIM), dev)
 
 
 def _idx_arg(cfg, idx, batch, dev, name="idx"):
-    import torch
+    torch = _torch()
     if not isinstance(idx, torch.Tensor) or idx.dim() != 3:
         raise ValueError(f"{name} must be a [batch][Hq][k] int32 tensor")
     k = int(idx.shape[-1])
@@ -266,7 +289,7 @@ def _idx_arg(cfg, idx, batch, dev, name="idx"):
 
 def _retrieve_outs(cfg, budget, batch, out_idx, out_score, workspace, n, device, dev):
     """Allocate what the caller left out and check the rest: (out_idx, out_score, workspace, ptrs)."""
-    import torch
+    torch = _torch()
     if out_idx is None:
         out_idx = torch.empty((batch, cfg.n_q_heads, budget.top_k), dtype=torch.int32, device=device)
     if workspace is None:
@@ -275,7 +298,8 @@ def _retrieve_outs(cfg, budget, batch, out_idx, out_score, workspace, n, device,
     rows = (batch, cfg.n_q_heads, budget.top_k)
     ptrs = (_arg(out_idx, "out_idx", torch.int32, rows, dev),
             _arg(out_score, "out_score", torch.float32, rows, dev, optional=True),
-            _arg(workspace, "workspace", torch.uint8, (None,), dev))
+            _arg(workspace, "workspace", torch.uint8,
+                 workspace.shape if isinstance(workspace, torch.Tensor) and workspace.dim() == 1 else (None,), dev))
     return out_idx, out_score, workspace, ptrs
 
 
@@ -299,7 +323,7 @@ class Index:
 
     def c(self, cfg=None, batch=None, dev=None):
         if cfg is not None:
-            import torch
+            torch = _torch()
             b = self.batch if batch is None else batch
             cap = cfg.capacity
             own = dev is None
@@ -316,11 +340,11 @@ class Index:
 
 
 def _keys_arg(cfg, keys, dev, name="keys"):
-    import torch
+    torch = _torch()
     if not isinstance(keys, torch.Tensor) or keys.dim() != 4:
         raise ValueError(f"{name} must be a [batch][Hkv][n][D] float16 tensor")
-    b = int(keys.shape[0])
-    return _arg(keys, name, torch.float16, (b, cfg.n_kv_heads, None, HEAD_DIM), dev), b
+    b = keys.shape[0]
+    return _arg(keys, name, torch.float16, (b, cfg.n_kv_heads, keys.shape[2], HEAD_DIM), dev), b
 
 
 def encode(cfg, index, keys, stream=None):
@@ -431,7 +455,7 @@ def retrieve_attend_noalloc(cfg, index, q, n, budget, K, V, scale, out_idx, out,
     static per-device scratch array (NOALLOC_SCRATCH_BYTES), for callers that cannot allocate.
     Allocates nothing, so out_idx [batch][Hq][k] int32 and out [batch][Hq][D] float32 must be
     given.  Calls that overlap on one device race on the shared array."""
-    import torch
+    torch = _torch()
     dev = []
     qp, batch = _q_arg(cfg, q, dev)
     kp, vp, cap = _kv_args(cfg, batch, K, V, kv_host_mapped, dev)
@@ -495,7 +519,7 @@ def group_attend(cfg, q, K, V, idx, scale, out=None, union_rows=None, kv_host_ma
     """sparse_attend with each distinct K/V row fetched once per KV head (quads of query heads
     attend over the union of their ascending lists); union_rows: optional int32 tensor
     [batch][Hkv][ceil(G/4)] that receives the number of rows fetched."""
-    import torch
+    torch = _torch()
     dev = []
     qp, batch = _q_arg(cfg, q, dev)
     kp, vp, cap = _kv_args(cfg, batch, K, V, kv_host_mapped, dev)
@@ -551,7 +575,7 @@ def retrieve_tiered_attend(cfg, index, q, n, budget, K_win, V_win, K, V, win, sc
 def offload_rows(K_src, V_src, src_row, K_dst, V_dst, dst_row, t, stream=None):
     """Copy rows [src_row, src_row + t) of every (sequence, KV head) of K_src/V_src to rows
     [dst_row, dst_row + t) of K_dst/V_dst (device or pinned host tensors [b][Hkv][cap][D])."""
-    import torch
+    torch = _torch()
     named = ((K_src, "K_src"), (V_src, "V_src"), (K_dst, "K_dst"), (V_dst, "V_dst"))
     for x, nm in named:
         if not isinstance(x, torch.Tensor) or x.dim() != 4:
