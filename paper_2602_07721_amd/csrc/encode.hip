@@ -18,22 +18,22 @@
 // Every float64 operation is an explicit round-to-nearest multiply or add
 // (no contraction), so the results do not depend on the compiler.
 //
-// Transform.  H (s (.) k) is a 128 x 128 matrix of +-1 times the keys: matrix
-// instructions (16x16x32, float16 in, float32 sums), made exact by splitting every
-// key coordinate x = hi + lo: lo = x less its rounding to a multiple of 2^-6 when
-// |x| < 8, else 0.  So |lo| <= 2^-7 in units of 2^-24 and 128 of them sum below
-// 2^24 units; |x| < 1024 gives hi in units of 2^-7 (2^-6 below 8) and a sum of at
-// most 2^24 of them.  Every partial sum of either part is then exact in float32 in
-// any order, and y = hi + lo in float64 is exact too.  lo is carried as 2^11 lo,
-// which is a normal float16 number.  A tile of 16 keys whose sums of squares may come from a
-// coordinate of 1024 or more (or are not finite) is redone by the float64 butterflies.
+// Transform.  H (s (.) k) is a 128 x 128 matrix of +-1 times the keys: 32 inputs at a time
+// on matrix instructions (16x16x32, float16 in, float32 sums), the four sums of a coordinate
+// combined in float64.  The products are made exact by splitting every key coordinate
+// x = hi + lo: lo = x less its rounding to a multiple of 2^-6 when |x| < 8, else 0.  So
+// |lo| <= 2^-7 in units of 2^-24, and 32 of them sum below 2^24 units; |x| < 4096 gives hi in
+// units of 2^-7 and a sum of at most 2^24 of them.  Every partial sum of either part is then
+// exact in float32 in any order, and so are hi + lo and the rest in float64.  lo is carried
+// as 2^11 lo, a normal float16 number.  A tile of 16 keys whose sums of squares may come from
+// a coordinate of 4096 or more (or are not finite) is redone by the float64 butterflies.
 //
 // Mapping: a wave takes 16 keys; lane 16 g + r holds coordinates [32 g, 32 g + 32) of
 // key r, i.e. subspaces 4g..4g+3, before and after the transform.  Coordinate 8 s +
 // 2 j + e (s < 16, j < 4, e < 2): a matrix step multiplies the 32 inputs of one j,
 // which lie in the 4 loaded uint4 as component j of each, so no data moves before
-// the product; output tile (J, T) holds (s, e) rows chosen so that lane group g gets
-// subspaces 4g + 2T, 4g + 2T + 1.
+// the product; output tile T holds (s, e) rows chosen so that lane group g gets
+// subspaces 4g + 2T, 4g + 2T + 1, and the 4 steps of a coordinate meet in one lane.
 //
 // Bins.  t_j compares Y_j with at most one of the 7 products tau_t^2 S_b: u = |y_j| /
 // sqrt(S_b) in float32 (error below 2^-20) falls in one of 64 buckets of [0, 1]; the
@@ -41,12 +41,13 @@
 // which is then compared in float64 as defined above.  Buckets are far narrower than
 // the gaps between thresholds (0.08 at least).
 //
-// What bounds it: vector issue.  A 16-key tile is about 830 vector instructions and 64
+// What bounds it: vector issue.  A 16-key tile is about 860 vector instructions and 16
 // matrix instructions (1665 vector ones with the transform as float64 butterflies and 7
-// compares per coordinate); the vector unit is busy 74% of the time with 3 waves per SIMD.
-// Measured: 8 x 131072 keys 238 -> 150 us (2.8 TB/s), 24 x 10007 keys 177 -> 45 us, most of
+// compares per coordinate); the vector unit is busy 3/4 of the time with 3 waves per SIMD.
+// Measured: 8 x 131072 keys 238 -> 142 us, 24 x 10007 keys 177 -> 42 us, most of
 // the second from blocks sized to fill the chip (launch_encode).  Two waves per SIMD, with
-// the matrix operands held in registers, took 14% longer.
+// the matrix operands held in registers, took 14% longer; summing all 128 inputs on the matrix
+// unit (64 instructions, no float64 stages) 2% longer.
 //
 // Each lane counts its 4 ids in an LDS histogram per block, added to global memory
 // once per block; records go through LDS so that a wave stores whole lines.
@@ -67,7 +68,7 @@ constexpr int kTile = 16;                           // keys per wave and iterati
 constexpr int kKeysPerIter = kThreads / 64 * kTile;
 constexpr int kBuckets = 64;                        // of u in [0, 1]; u may round up to 1: one more entry
 constexpr int kBucketLut = kBuckets + 1;
-constexpr int kFrags = 14;                          // matrix operands: 2 tiles x 4 steps, 3 of them also negated
+constexpr int kFrags = 8;                           // matrix operands: 2 tiles x 4 steps
 constexpr int kStageRow = kRec + 16;                // bytes per staged record (padded against bank conflicts)
 
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
@@ -111,7 +112,7 @@ __device__ __forceinline__ double tree8_sum(const double* v) {
 // id_slot of the 4 bytes of a word.
 __device__ __forceinline__ uint32_t id_slot4(uint32_t w) {
     const uint32_t b5 = (w >> 5) & 0x01010101u, b6 = (w >> 6) & 0x01010101u, b7 = (w >> 7) & 0x01010101u;
-    return w ^ ((b5 << 3) - b5) ^ (b6 | b6 << 3 | b6 << 4) ^ ((b7 << 4) - (b7 << 1));
+    return w ^ (b5 | b5 << 1 | b5 << 2) ^ (b6 | b6 << 3 | b6 << 4) ^ (b7 << 1 | b7 << 2 | b7 << 3);
 }
 
 // Both float16 of a word as float64.
@@ -246,7 +247,7 @@ struct Summaries {
 // inlined: it is rare, and its registers would be the kernel's.
 template <bool kAlpha>
 __device__ __attribute__((noinline)) Summaries general_tile(const __half* src, int64_t base, int64_t k_end,
-                                                            uint32_t smask, const double* s_a, const QuantConsts& qc) {
+                                                            uint32_t smask, const double* s_a, const double* s_tau2) {
     const int lane = threadIdx.x & 63;
     uint4 raw[4];
     load_part(src, base, k_end, lane, raw);
@@ -258,7 +259,7 @@ __device__ __attribute__((noinline)) Summaries general_tile(const __half* src, i
         double Y[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) Y[j] = __dmul_rn(x[8 * b + j], x[8 * b + j]);
-        r.s[b] = summarise_any<kAlpha>(x + 8 * b, tree8_sum(Y), qc.tau2, s_a);
+        r.s[b] = summarise_any<kAlpha>(x + 8 * b, tree8_sum(Y), s_tau2, s_a);
         __builtin_amdgcn_sched_barrier(0);
     }
     return r;
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
     const __half* __restrict__ keys, int64_t n_src, int64_t src_stride, int64_t keys_per_block, int64_t row0,
     int64_t capacity, uint8_t* __restrict__ ids, uint8_t* __restrict__ rec,
     uint32_t* __restrict__ counts, SignBits sb, QuantConsts qc) {
-    __shared__ double s_a[8];
+    __shared__ double s_a[8], s_tau2[7];
     __shared__ Buckets s_bk;
     __shared__ uint4 s_frag[kRotate ? kFrags : 1][64];
     __shared__ __align__(16) uint8_t s_stage[kThreads / 64][kTile * kStageRow];
@@ -289,8 +290,7 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
 
     const uint32_t smask = g == 0 ? sb.w[0] : g == 1 ? sb.w[1] : g == 2 ? sb.w[2] : sb.w[3];
     // Matrix operands, one uint4 per lane: output (s, e) of tile T in row r16, inputs
-    // 8 (4g + c) + 2 j + e', the rotation's signs folded in.  Tile (J, T) takes step j as it is
-    // or negated (odd popcount of J & j).
+    // 8 (4g + c) + 2 j + e', the rotation's signs folded in.
     if (kRotate) {
         for (int f = wave; f < 8; f += waves) {
             const int T = f >> 2, j = f & 3;
@@ -303,12 +303,10 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
                        (__popc(so & (4 * g + c)) & 1 ? 0x80008000u : 0u) ^ (r16 & 1 ? 0x80000000u : 0u);
             }
             s_frag[f][lane] = make_uint4(w[0], w[1], w[2], w[3]);
-            if (j)
-                s_frag[8 + 3 * T + j - 1][lane] = make_uint4(w[0] ^ 0x80008000u, w[1] ^ 0x80008000u,
-                                                             w[2] ^ 0x80008000u, w[3] ^ 0x80008000u);
         }
     }
     if (tid < 8) s_a[tid] = qc.a[tid];
+    if (tid < 7) s_tau2[tid] = qc.tau2[tid];
     for (int i = tid; i < kBucketLut; i += (int)blockDim.x) {
         // Bins surely passed by every u that may fall in bucket i, and the next threshold.
         const double lo = fmax(0.0, ((double)i - 1e-3) / kBuckets);
@@ -345,44 +343,46 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
                 split_pair(cur[c].z, &hi[2][c], &lo[2][c]);
                 split_pair(cur[c].w, &hi[3][c], &lo[3][c]);
             }
-            // Read for every tile: 56 registers less than holding them, which is another wave per SIMD.
+            // Read for every tile: 32 registers less than holding them, which is another wave per SIMD.
             int at = lane;
             asm volatile("" : "+v"(at));
 #pragma unroll
             for (int T = 0; T < 2; ++T) {
-                f16x8 A[4], N[3];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) A[j] = __builtin_bit_cast(f16x8, s_frag[4 * T + j][at]);
-#pragma unroll
-                for (int j = 0; j < 3; ++j) N[j] = __builtin_bit_cast(f16x8, s_frag[8 + 3 * T + j][at]);
                 f32x4 ah[4], al[4];
 #pragma unroll
-                for (int J = 0; J < 4; ++J) {
-                    ah[J] = al[J] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const f16x8 m = (__builtin_popcount(J & j) & 1) ? N[j ? j - 1 : 0] : A[j];
-                        ah[J] = __builtin_amdgcn_mfma_f32_16x16x32_f16(m, frag(hi[j]), ah[J], 0, 0, 0);
-                        al[J] = __builtin_amdgcn_mfma_f32_16x16x32_f16(m, frag(lo[j]), al[J], 0, 0, 0);
-                    }
+                for (int j = 0; j < 4; ++j) {
+                    const f16x8 m = __builtin_bit_cast(f16x8, s_frag[4 * T + j][at]);
+                    ah[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(m, frag(hi[j]), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    al[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(m, frag(lo[j]), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
                 }
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
                     double y[8], Y[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        y[j] = __fma_rn((double)al[j >> 1][2 * q + (j & 1)], 0x1p-11, (double)ah[j >> 1][2 * q + (j & 1)]);
-                        Y[j] = __dmul_rn(y[j], y[j]);
+                    for (int e = 0; e < 2; ++e) {
+                        // The four steps' sums combined over j by two butterfly stages.
+                        double v[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            v[j] = __fma_rn((double)al[j][2 * q + e], 0x1p-11, (double)ah[j][2 * q + e]);
+                        const double t0 = __dadd_rn(v[0], v[1]), t1 = __dsub_rn(v[0], v[1]);
+                        const double t2 = __dadd_rn(v[2], v[3]), t3 = __dsub_rn(v[2], v[3]);
+                        y[e] = __dadd_rn(t0, t2);
+                        y[2 + e] = __dadd_rn(t1, t3);
+                        y[4 + e] = __dsub_rn(t0, t2);
+                        y[6 + e] = __dsub_rn(t1, t3);
                     }
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) Y[j] = __dmul_rn(y[j], y[j]);
                     const double S = tree8_sum(Y);
                     total += S;
                     sm[2 * T + q] = summarise<kAlpha>(y, Y, S, s_bk, s_a);
                 }
                 __builtin_amdgcn_sched_barrier(0);  // the halves of a tile share registers
             }
-            // A coordinate of 1024 makes the key's squares sum to 2^27 over its 4 lanes.
-            if (__any(!(total < 0x1p24))) {
-                const Summaries again = general_tile<kAlpha>(src, base, k_end, smask, s_a, qc);
+            // A coordinate of 4096 makes the key's squares sum to 2^31 over its 4 lanes.
+            if (__any(!(total < 0x1p28))) {
+                const Summaries again = general_tile<kAlpha>(src, base, k_end, smask, s_a, s_tau2);
 #pragma unroll
                 for (int b = 0; b < 4; ++b) sm[b] = again.s[b];
             }
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
                 for (int h = 0; h < 4; ++h) widen(w[h], &y[2 * h], &y[2 * h + 1]);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) Y[j] = __dmul_rn(y[j], y[j]);
-                sm[b] = summarise_any<kAlpha>(y, tree8_sum(Y), qc.tau2, s_a);
+                sm[b] = summarise_any<kAlpha>(y, tree8_sum(Y), s_tau2, s_a);
             }
         }
 

@@ -1,6 +1,6 @@
 """GPU parity of the encode kernel where its transform and its bins can go wrong: key counts at
 the edges of a 16-key tile and of a block, both ways of counting clusters, and keys whose
-coordinates reach the limits of the exact float16 split (rounding boundary 8, size limit 1024,
+coordinates reach the limits of the exact float16 split (rounding boundary 8, size limit 4096,
 subnormals, zeros of both signs, infinities next to ordinary keys).  Every byte against the oracle."""
 
 import numpy as np
@@ -23,7 +23,7 @@ def _edge_keys(n, seed):
     K = np.where((kind == 1)[:, None], few, K)  # many transformed coordinates exactly 0
     at8 = np.array([8.0, -8.0, 7.996, -7.996, 8.008, 15.99, 16.0, -4.0])
     K = np.where((kind == 2)[:, None], r.choice(at8, size=(n, 128)), K)
-    K = np.where((kind == 3)[:, None], r.choice([1023.5, -1023.5, 2.0 ** -24, 0.00781], size=(n, 128)), K)
+    K = np.where((kind == 3)[:, None], r.choice([1023.5, -4094.0, 2.0 ** -24, 0.00781], size=(n, 128)), K)
     K = np.where((kind == 4)[:, None], r.choice([2.0 ** -24, -(2.0 ** -24), 2.0 ** -14, 3e-6], size=(n, 128)), K)
     K = np.where((kind == 5)[:, None], np.where(r.random((n, 128)) < 0.5, 0.0, -0.0), K)
     K = np.where((kind == 6)[:, None], r.standard_normal((n, 128)) + 40.0 * (np.arange(128) % 37 == 0), K)
@@ -31,9 +31,9 @@ def _edge_keys(n, seed):
 
 
 def _large(K, every):
-    """Coordinates past the split's limit (1024 and the largest float16) in every `every`-th key."""
+    """Coordinates past the split's limit (4096 and the largest float16) in every `every`-th key."""
     K = K.copy()
-    K[::every, 5] = np.float16(1024.0)
+    K[::every, 5] = np.float16(4096.0)
     K[every // 2::every, 77] = np.float16(-65504.0)
     return K
 
