@@ -78,15 +78,22 @@ __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
     return v;
 }
 
+// Sum of x over the 16 lanes of each row of the wave, in every lane (DPP adds as below).
+// Every lane of the row must be active.
+__device__ __forceinline__ float row_sum_f32(float x) {
+    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
+    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
+    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, false));  // row_half_mirror
+    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x140, 0xF, 0xF, false));  // row_mirror
+    return x;
+}
+
 // Sum of x over the 64 lanes of the wave, the same value in every lane, through
 // DPP adds inside each row of 16 lanes (quad partners, then the mirrored lane in
 // the half row and in the row) and the four row sums read out by readlane, added
 // in row order.  Every lane of the wave must be active.
 __device__ __forceinline__ float wave_sum_f32(float x) {
-    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
-    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
-    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, false));  // row_half_mirror
-    x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x140, 0xF, 0xF, false));  // row_mirror
+    x = row_sum_f32(x);
     const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 0));
     const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16));
     const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 32));
