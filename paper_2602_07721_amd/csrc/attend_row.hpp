@@ -59,6 +59,14 @@ __device__ __forceinline__ void unpack8_half(const uint4 v, float* f) {
     }
 }
 
+// Any value: a row segment that is not loaded is never used, and setting it would cost
+// 4 instructions a row.
+__device__ __forceinline__ uint4 unset_uint4() {
+    uint4 v;
+    asm volatile("" : "=v"(v.x), "=v"(v.y), "=v"(v.z), "=v"(v.w));
+    return v;
+}
+
 // Sum of x over the 16 lanes of each row of the wave, in every lane, through
 // DPP adds (no LDS): partners lane ^ 1 and lane ^ 2 (quad_perm), then the
 // mirrored lane in the half row and in the row.  After the quad steps the lanes
@@ -106,24 +114,37 @@ __device__ __forceinline__ void attend_row(uint4 qv, const __half* __restrict__ 
         for (int d = 0; d < 8; ++d) acc[v][d] = 0.f;
     }
 
+    // Capacities fit 30 bits; without a window cache the entries need no test for it.
+    const uint32_t kv_rows = (uint32_t)kv_capacity, win_rows = (uint32_t)win_capacity;
+    const uint4* Kl = reinterpret_cast<const uint4*>(K) + l16;
+    const uint4* Vl = reinterpret_cast<const uint4*>(V) + l16;
     for (int base = 0; base < k; base += kAtGroups * kRows) {
         int32_t key[kAtUnroll];  // row u of slot v at v kRows + u
         uint4 kc[kAtUnroll], vc[kAtUnroll];
+        // Every list entry read before the first is used.
+#pragma unroll
+        for (int i = 0; i < kAtUnroll; ++i)
+            key[i] = list[min(base + grp16 + kGroups * (i / kRows) + kAtGroups * (i % kRows), k - 1)];
 #pragma unroll
         for (int i = 0; i < kAtUnroll; ++i) {
-            const int r = base + grp16 + kGroups * (i / kRows) + kAtGroups * (i % kRows);
-            key[i] = r < k ? list[r] : -1;
-            const bool win = key[i] >= kWinRow;
-            const int64_t rowi = win ? key[i] - kWinRow : key[i];
-            if (rowi >= (win ? win_capacity : kv_capacity)) key[i] = -1;
-            kc[i] = make_uint4(0, 0, 0, 0);
-            vc[i] = make_uint4(0, 0, 0, 0);
-            // A held row (entry <= -2 with prow) is read from LDS where it is used.
-            if (prow == nullptr && key[i] < 0) key[i] = -1;
-            if (key[i] >= 0) {
-                const int64_t off = rowi * kD;
-                kc[i] = reinterpret_cast<const uint4*>((win ? Kw : K) + off)[l16];
-                vc[i] = reinterpret_cast<const uint4*>((win ? Vw : V) + off)[l16];
+            if (base + grp16 + kGroups * (i / kRows) + kAtGroups * (i % kRows) >= k) key[i] = -1;
+            uint32_t rowi = (uint32_t)key[i], cap = kv_rows;  // a negative entry is past every capacity
+            const uint4 *kb = Kl, *vb = Vl;
+            if (win_rows) {
+                const bool win = key[i] >= kWinRow;
+                rowi = win ? (uint32_t)(key[i] - kWinRow) : rowi;
+                cap = win ? win_rows : cap;
+                kb = win ? reinterpret_cast<const uint4*>(Kw) + l16 : kb;
+                vb = win ? reinterpret_cast<const uint4*>(Vw) + l16 : vb;
+            }
+            const bool in = rowi < cap;
+            if (!in && (prow == nullptr || key[i] >= 0)) key[i] = -1;  // else held (<= -2) or -1
+            kc[i] = unset_uint4();
+            vc[i] = unset_uint4();
+            if (in) {
+                const int64_t off = (int64_t)rowi * (kD / 8);
+                kc[i] = kb[off];
+                vc[i] = vb[off];
             }
         }
         float dot[kAtUnroll];
