@@ -294,11 +294,13 @@ constexpr int64_t kRrWideGrid = 2048;
 // Whether every rerank block derives its row's threshold itself, without a threshold launch.
 // Pays where the launch counts and few histograms are read: 1 x 8 heads x 4096 keys 33.7 ->
 // 31.3 us a call, 32 x 32K 35.3 -> 33.0, 256 x 32K (2048 blocks) 51.8 -> 49.0, 32 x 128K
-// (32 chunks) 44.7 -> 42.7.  Past one round of blocks the rerank's 128-thread blocks lose
-// what the launch saves (512 x 32K: 86.9 -> 88.5).
-constexpr int kFoldChunks = 32;
+// (32 chunks) 44.7 -> 42.7.  Past one round of blocks it takes 256-thread blocks (4 waves to
+// read the histograms) where the plain rerank is faster in 128, and pays up to 16 chunks:
+// 1024 x 16K 95.4 -> 90.7, 512 x 32K 77.6 -> 76.4, 384 x 64K 100.8 -> 100.1.
+constexpr int kFoldChunks = 32, kFoldChunksLarge = 16;
 inline bool fold_threshold(const RetrieveArgs& a) {
-    return a.n_chunks <= kFoldChunks && a.n_chunks * a.batch * a.hq <= kRrWideGrid;
+    const bool one_round = a.n_chunks * a.batch * a.hq <= kRrWideGrid;
+    return a.n_chunks <= (one_round ? kFoldChunks : kFoldChunksLarge);
 }
 
 hipError_t launch_query_lut(const RetrieveArgs& a, hipStream_t s);

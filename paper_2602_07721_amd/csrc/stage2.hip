@@ -1031,8 +1031,10 @@ hipError_t launch_compact_rerank(const RetrieveArgs& a, hipStream_t s) {
     const bool fold = fold_threshold(a);
     if (blocks <= kRrWidestGrid)
         fold ? PARISKV_RERANK(512, true) : PARISKV_RERANK(512, false);
+    else if (fold)
+        PARISKV_RERANK(256, true);
     else if (blocks <= kRrWideGrid)
-        fold ? PARISKV_RERANK(256, true) : PARISKV_RERANK(256, false);
+        PARISKV_RERANK(256, false);
     else
         PARISKV_RERANK(128, false);
 #undef PARISKV_RERANK
