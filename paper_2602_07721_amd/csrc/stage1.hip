@@ -106,6 +106,29 @@ __device__ __forceinline__ void sort128_desc(int64_t (&key)[2], int lane) {
     }
 }
 
+// The same sort of 32-bit keys.
+__device__ __forceinline__ void sort128_desc(uint32_t (&key)[2], int lane) {
+#pragma unroll
+    for (int k = 2; k <= 128; k <<= 1) {
+#pragma unroll
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            if (j >= 2) {
+                const uint64_t keep_max = ~(lane_bit(log2i(j) - 1) ^ lane_bit(log2i(k) - 1));
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const uint32_t o = lane_xor(key[r], j >> 1, lane);
+                    key[r] = select_mask(~(__ballot(o > key[r]) ^ keep_max), o, key[r]);
+                }
+            } else {
+                const uint64_t swap = ~(__ballot(key[0] < key[1]) ^ ~lane_bit(log2i(k) - 1));
+                const uint32_t x = key[0], y = key[1];
+                key[0] = select_mask(swap, y, x);
+                key[1] = select_mask(swap, x, y);
+            }
+        }
+    }
+}
+
 // The histogram floor v_lo of a query head: the collision scan histograms only scores
 // S >= v_lo.  It is the integer part of a normal-law estimate of the selection threshold with the
 // subspaces' bonus weights taken as independent: mean sum_b E[bonus_b], variance
@@ -142,9 +165,14 @@ __device__ __forceinline__ uint32_t hist_floor(float2 st, int64_t n, int64_t c_e
 // 45K) 45.9 -> 44.4.  From 64 quads on, blocks of 4 subspaces that share the transforms already
 // fill the chip (64 quads of 128K keys 128.2 -> 128.5 with 16 blocks).
 constexpr int64_t kLutNarrow = 32;
+// Past this many (4 blocks of 16 waves a quad: one block per CU) the waves compete for issue
+// and sort 32-bit keys first: 128 quads 9.2 -> 8.5 us, 256 quads 16.0 -> 14.9.  Below, a wave
+// that has to sort again ends the kernel later than the shorter sort makes up (64 quads: a
+// call of 126.9 us takes 127.4).
+constexpr int64_t kLutOneBlock = 64;
 
 // kSubs: subspaces per block, one wave per (head slot, subspace).
-template <int kSubs>
+template <int kSubs, bool kShort>
 __global__ __launch_bounds__(256 * kSubs) void query_lut_kernel(RetrieveArgs a) {
     constexpr int kGroups = kB / kSubs;            // blocks per quad
     __shared__ double s_z[4][kD];
@@ -232,20 +260,51 @@ __global__ __launch_bounds__(256 * kSubs) void query_lut_kernel(RetrieveArgs a) 
         // and the other members follow in the reverse order: the one of the
         // representative at position i has rank 255 - i (proxy -|p| desc, and for
         // equal |p| the representatives' id order reverses under c ^ 255).
-        int64_t key[2];
+        double p[2];
+        int rep[2];
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             const int c = 2 * lane + r;
-            double p = 0.0;
+            p[r] = 0.0;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) p = ((c >> j) & 1) ? __dsub_rn(p, zb[j]) : __dadd_rn(p, zb[j]);
-            // p is an exact multiple of 2^-24 with |p| < 2^26: exact as an integer.
-            const int64_t pi = (int64_t)(p * 16777216.0);
-            const bool neg = pi < 0;
-            const int rep = neg ? c ^ 255 : c;
-            key[r] = (neg ? -pi : pi) * 256 + (255 - rep);  // descending key: |proxy| desc, then id asc
+            for (int j = 0; j < 8; ++j) p[r] = ((c >> j) & 1) ? __dsub_rn(p[r], zb[j]) : __dadd_rn(p[r], zb[j]);
+            rep[r] = p[r] < 0.0 ? c ^ 255 : c;
         }
-        sort128_desc(key, lane);
+        // With kShort they are sorted as 32-bit keys: |p| scaled to 24 bits (sum |z_j|, the
+        // largest, below 2^24) over the id.  The scaling keeps the order, so where no two
+        // neighbours of the sorted keys share the 24 bits the order is exact; otherwise (equal
+        // or nearly equal proxies, about 1 ranking in 700 of continuous coordinates), as
+        // without kShort, exact 64-bit keys are sorted.
+        uint32_t key[2] = {0u, 0u};
+        bool exact = !kShort;
+        if constexpr (kShort) {
+            double top = 0.0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) top = __dadd_rn(top, fabs(zb[j]));
+            const double to24 = 16777000.0 * __builtin_amdgcn_rcp(top);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                uint32_t q;
+                asm("v_cvt_u32_f64 %0, %1" : "=v"(q) : "v"(__dmul_rn(fabs(p[r]), to24)));  // NaN: 0
+                key[r] = min(q, 0xffffffu) << 8 | (uint32_t)(255 - rep[r]);
+            }
+            sort128_desc(key, lane);
+            const uint32_t next = (uint32_t)__builtin_amdgcn_ds_bpermute(min(lane + 1, 63) << 2, (int)key[0]);
+            const bool same = (key[0] ^ key[1]) < 256u || (lane < 63 && (key[1] ^ next) < 256u);
+            exact = __any(same || !(top > 0.0));
+        }
+        if (exact) {
+            int64_t wide[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                // p is an exact multiple of 2^-24 with |p| < 2^26: exact as an integer.
+                const int64_t pi = (int64_t)(p[r] * 16777216.0);
+                wide[r] = (pi < 0 ? -pi : pi) * 256 + (255 - rep[r]);  // descending key: |proxy| desc, then id asc
+            }
+            sort128_desc(wide, lane);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) key[r] = (uint32_t)wide[r];
+        }
         // Representatives at positions 2 lane + r (r = 0, 1), ranks 2 lane + r; the
         // other members at ranks 255 - (2 lane + r).  Exclusive prefix of cluster
         // counts in rank order -> start rank P(c): the representatives' by a wave scan,
@@ -671,10 +730,16 @@ __global__ __launch_bounds__(kThrThreads) void threshold_kernel(RetrieveArgs a) 
 hipError_t launch_query_lut(const RetrieveArgs& a, hipStream_t s) {
     const int64_t quads = (int64_t)a.batch * a.hkv * a.quads;
     const ProfEvents pe = prof_begin("query_lut");
+#define PARISKV_QUERY(SUBS, SHORT)                                                                       \
+    hipExtLaunchKernelGGL((query_lut_kernel<SUBS, SHORT>), dim3((unsigned)(quads * (kB / SUBS))), dim3(256 * SUBS), 0, \
+                          s, pe.start, pe.stop, 0, a)
     if (quads <= kLutNarrow)
-        hipExtLaunchKernelGGL(query_lut_kernel<1>, dim3((unsigned)(quads * 16)), dim3(256), 0, s, pe.start, pe.stop, 0, a);
+        PARISKV_QUERY(1, false);
+    else if (quads <= kLutOneBlock)
+        PARISKV_QUERY(4, false);
     else
-        hipExtLaunchKernelGGL(query_lut_kernel<4>, dim3((unsigned)(quads * 4)), dim3(1024), 0, s, pe.start, pe.stop, 0, a);
+        PARISKV_QUERY(4, true);
+#undef PARISKV_QUERY
     return hipGetLastError();
 }
 

@@ -42,9 +42,11 @@ def _run(batch, hkv, G, n, bud, flags=0, seed=71):
 @pytest.mark.parametrize("batch,hkv,G,n,bud", [
     # the scan reads a chunk in rounds of 2048 keys
     (1, 1, 4, 2047, (200, 400, 30)), (1, 1, 3, 2049, (200, 400, 30)), (1, 2, 4, 4096 + 2048, (300, 600, 40)),
-    # 512 rerank blocks (512 threads each), 576 (256 threads), 2048 and 2080 (128 threads, threshold kernel)
+    # 512 rerank blocks (512 threads each), 576 and 2048 (256 threads), 2080 (past one round)
     (2, 8, 4, 8 * 4096 - 5, (700, 1400, 64)), (2, 8, 4, 8 * 4096 + 3, (700, 1400, 64)),
     (16, 8, 4, 4 * 4096, (300, 600, 32)), (13, 8, 5, 3 * 4096 + 1, (300, 600, 32)),
+    # past one round of blocks: 16 chunks, the most whose threshold the rerank derives there, and 17
+    (1, 9, 16, 16 * 4096, (600, 1200, 40)), (1, 9, 16, 16 * 4096 + 9, (600, 1200, 40)),
     # 32 chunks, the most whose threshold the rerank derives, and 33
     (1, 1, 2, 32 * 4096, (2048, 4096, 100)), (1, 1, 2, 32 * 4096 + 1, (2048, 4096, 100)),
 ])
@@ -83,10 +85,32 @@ def test_top_k_block_edges(batch, hkv, G, n, bud):
     _run(batch, hkv, G, n, bud)
 
 
-@pytest.mark.parametrize("batch,hkv,G", [(4, 8, 4), (11, 3, 4), (4, 4, 8), (11, 1, 10), (3, 11, 1)])
+@pytest.mark.parametrize("batch,hkv,G", [(4, 8, 4), (11, 3, 4), (4, 4, 8), (11, 1, 10), (3, 11, 1), (8, 8, 4), (13, 5, 2),
+                                         (11, 3, 7)])
 def test_query_block_edges(batch, hkv, G):
-    # 32 and 33 quads of query heads: 1 and 4 subspaces per block; partial quads
+    # 32, 33, 64 and 65 quads of query heads: 1 and 4 subspaces per block, rankings by 64-bit
+    # and by 32-bit keys; partial quads
     _run(batch, hkv, G, 1500, (200, 400, 20))
+
+
+def test_tied_rankings_by_short_keys():
+    # queries with a few equal coordinates: most proxies tie, exactly or within 24 bits
+    batch, hkv, G, n = 17, 4, 4, 700
+    wc = workloads.Config("ties", batch=batch, n_kv_heads=hkv, q_per_kv=G, n=n, n_cand=90, n_collide=180, top_k=9, seed=73)
+    K, V = workloads.layer_kv(wc)
+    Q, _ = workloads.layer_queries(wc, K)
+    r = np.random.default_rng(5)
+    Q[:8] = (r.integers(-1, 2, size=Q[:8].shape) * (r.random(Q[:8].shape) < 0.03)).astype(np.float16)
+    Q[8] = Q[8, :, :1] * (r.random(Q[8].shape) < 0.1) + (2.0 ** -20 * r.integers(-1, 2, size=Q[8].shape)).astype(np.float16)
+    signs = workloads.rotation_signs(73)
+    budget = pk.Budget(90, 180, 9)
+    run = GpuRun(K, V, Q, signs, G, budget, SCALE).retrieve()
+    inter = run.intermediates()
+    for s in (0, 5, 8, 16):
+        for h in range(hkv):
+            orc = oracle_group(K[s, h], signs)
+            for g in range(G):
+                check_head(inter, s, h, g, G, Q[s, h * G + g], orc, signs, budget, n)
 
 
 @pytest.mark.parametrize("batch,C,k", [(1, 700, 50), (1, 2000, 200), (9, 2000, 100), (9, 4000, 200)])
