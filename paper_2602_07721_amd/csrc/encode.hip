@@ -41,10 +41,10 @@
 // which is then compared in float64 as defined above.  Buckets are far narrower than
 // the gaps between thresholds (0.08 at least).
 //
-// What bounds it: vector issue.  A 16-key tile is about 860 vector instructions and 16
+// What bounds it: vector issue.  A 16-key tile is about 830 vector instructions and 16
 // matrix instructions (1665 vector ones with the transform as float64 butterflies and 7
 // compares per coordinate); the vector unit is busy 3/4 of the time with 3 waves per SIMD.
-// Measured: 8 x 131072 keys 238 -> 142 us, 24 x 10007 keys 177 -> 42 us, most of
+// Measured: 8 x 131072 keys 238 -> 136 us, 24 x 10007 keys 177 -> 41 us, most of
 // the second from blocks sized to fill the chip (launch_encode).  Two waves per SIMD, with
 // the matrix operands held in registers, took 14% longer; summing all 128 inputs on the matrix
 // unit (64 instructions, no float64 stages) 2% longer.
@@ -66,8 +66,8 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kTile = 16;                           // keys per wave and iteration
 constexpr int kKeysPerIter = kThreads / 64 * kTile;
-constexpr int kBuckets = 64;                        // of u in [0, 1]; u may round up to 1: one more entry
-constexpr int kBucketLut = kBuckets + 1;
+constexpr int kBuckets = 64;                        // of u in [0, 1]; u may round up past 1: more entries
+constexpr int kBucketLut = 2 * kBuckets;            // (a power of two, so that a mask bounds the index)
 constexpr int kFrags = 8;                           // matrix operands: 2 tiles x 4 steps
 constexpr int kStageRow = kRec + 16;                // bytes per staged record (padded against bank conflicts)
 
@@ -168,15 +168,17 @@ __device__ __forceinline__ Summary summarise_any(const double* y, double S, cons
 // Finite y, none of them -0: one compare per coordinate, chosen by its bucket.
 template <bool kAlpha>
 __device__ __forceinline__ Summary summarise(const double* y, const double* Y, double S, const Buckets& s_bk, const double* s_a) {
-    // |u| kBuckets <= kBuckets (1 + 2^-20); S = 0 gives NaN, which converts to bucket 0.
+    // |u| kBuckets <= kBuckets (1 + 2^-20); S = 0 gives NaN, whose masked bits are bucket 0.
     const float rs = (float)kBuckets * __builtin_amdgcn_rsqf((float)S);
     double P[8];
     uint32_t code = 0;
 #pragma unroll
     for (int j = 7; j >= 0; --j) {
-        uint32_t bucket;
-        asm("v_cvt_u32_f32 %0, %1" : "=v"(bucket) : "v"(fabsf((float)y[j]) * rs));
-        const uint32_t t = s_bk.passed[bucket][0] + (Y[j] >= __dmul_rn(s_bk.next[bucket], S) ? 1u : 0u);
+        // u kBuckets + 2^20 leaves the bucket in bits 3..9 of the sum (rounded to eighths), which is
+        // its byte offset in the 8-byte entries: one mask instead of a conversion and a shift.
+        const uint32_t at = __float_as_uint(__fmaf_rn(fabsf((float)y[j]), rs, 0x1p20f)) & (8u * (kBucketLut - 1));
+        const uint32_t t = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(s_bk.passed) + at) +
+                           (Y[j] >= __dmul_rn(*reinterpret_cast<const double*>(reinterpret_cast<const char*>(s_bk.next) + at), S) ? 1u : 0u);
         P[j] = __dmul_rn(s_a[t], fabs(y[j]));
         code = __builtin_amdgcn_alignbit(code, (uint32_t)__double2hiint(y[j]), 31);  // code << 1 | sign
         code = code << 3 | t;
@@ -308,8 +310,9 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
     if (tid < 8) s_a[tid] = qc.a[tid];
     if (tid < 7) s_tau2[tid] = qc.tau2[tid];
     for (int i = tid; i < kBucketLut; i += (int)blockDim.x) {
-        // Bins surely passed by every u that may fall in bucket i, and the next threshold.
-        const double lo = fmax(0.0, ((double)i - 1e-3) / kBuckets);
+        // Bins surely passed by every u that may fall in bucket i (rounding may lift it by 1/16
+        // of a bucket), and the next threshold.
+        const double lo = fmax(0.0, ((double)i - 0.07) / kBuckets);
         uint32_t c = 0;
         double next = __builtin_huge_val();
 #pragma unroll
