@@ -171,6 +171,14 @@ constexpr int64_t kLutNarrow = 32;
 // call of 126.9 us takes 127.4).
 constexpr int64_t kLutOneBlock = 64;
 
+// Proxy of centroid c (bit 7 clear or not): sum_j +-z_j, minus where bit j of c is set.
+__device__ __forceinline__ double proxy(const double (&zb)[8], int c) {
+    double p = 0.0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p = ((c >> j) & 1) ? __dsub_rn(p, zb[j]) : __dadd_rn(p, zb[j]);
+    return p;
+}
+
 // kSubs: subspaces per block, one wave per (head slot, subspace).
 template <int kSubs, bool kShort>
 __global__ __launch_bounds__(256 * kSubs) void query_lut_kernel(RetrieveArgs a) {
@@ -260,50 +268,45 @@ __global__ __launch_bounds__(256 * kSubs) void query_lut_kernel(RetrieveArgs a) 
         // and the other members follow in the reverse order: the one of the
         // representative at position i has rank 255 - i (proxy -|p| desc, and for
         // equal |p| the representatives' id order reverses under c ^ 255).
-        double p[2];
-        int rep[2];
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int c = 2 * lane + r;
-            p[r] = 0.0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) p[r] = ((c >> j) & 1) ? __dsub_rn(p[r], zb[j]) : __dadd_rn(p[r], zb[j]);
-            rep[r] = p[r] < 0.0 ? c ^ 255 : c;
-        }
+        int64_t key[2];
         // With kShort they are sorted as 32-bit keys: |p| scaled to 24 bits (sum |z_j|, the
         // largest, below 2^24) over the id.  The scaling keeps the order, so where no two
         // neighbours of the sorted keys share the 24 bits the order is exact; otherwise (equal
         // or nearly equal proxies, about 1 ranking in 700 of continuous coordinates), as
         // without kShort, exact 64-bit keys are sorted.
-        uint32_t key[2] = {0u, 0u};
-        bool exact = !kShort;
+        bool exact = true;
         if constexpr (kShort) {
             double top = 0.0;
 #pragma unroll
             for (int j = 0; j < 8; ++j) top = __dadd_rn(top, fabs(zb[j]));
             const double to24 = 16777000.0 * __builtin_amdgcn_rcp(top);
+            uint32_t k32[2];
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
+                const int c = 2 * lane + r;
+                const double p = proxy(zb, c);
                 uint32_t q;
-                asm("v_cvt_u32_f64 %0, %1" : "=v"(q) : "v"(__dmul_rn(fabs(p[r]), to24)));  // NaN: 0
-                key[r] = min(q, 0xffffffu) << 8 | (uint32_t)(255 - rep[r]);
+                asm("v_cvt_u32_f64 %0, %1" : "=v"(q) : "v"(__dmul_rn(fabs(p), to24)));  // NaN: 0
+                k32[r] = min(q, 0xffffffu) << 8 | (uint32_t)(255 - (p < 0.0 ? c ^ 255 : c));
             }
-            sort128_desc(key, lane);
-            const uint32_t next = (uint32_t)__builtin_amdgcn_ds_bpermute(min(lane + 1, 63) << 2, (int)key[0]);
-            const bool same = (key[0] ^ key[1]) < 256u || (lane < 63 && (key[1] ^ next) < 256u);
+            sort128_desc(k32, lane);
+            const uint32_t next = (uint32_t)__builtin_amdgcn_ds_bpermute(min(lane + 1, 63) << 2, (int)k32[0]);
+            const bool same = (k32[0] ^ k32[1]) < 256u || (lane < 63 && (k32[1] ^ next) < 256u);
             exact = __any(same || !(top > 0.0));
+            key[0] = k32[0];
+            key[1] = k32[1];
         }
         if (exact) {
-            int64_t wide[2];
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
+                const int c = 2 * lane + r;
                 // p is an exact multiple of 2^-24 with |p| < 2^26: exact as an integer.
-                const int64_t pi = (int64_t)(p[r] * 16777216.0);
-                wide[r] = (pi < 0 ? -pi : pi) * 256 + (255 - rep[r]);  // descending key: |proxy| desc, then id asc
+                const int64_t pi = (int64_t)(proxy(zb, c) * 16777216.0);
+                const bool neg = pi < 0;
+                const int rep = neg ? c ^ 255 : c;
+                key[r] = (neg ? -pi : pi) * 256 + (255 - rep);  // descending key: |proxy| desc, then id asc
             }
-            sort128_desc(wide, lane);
-#pragma unroll
-            for (int r = 0; r < 2; ++r) key[r] = (uint32_t)wide[r];
+            sort128_desc(key, lane);
         }
         // Representatives at positions 2 lane + r (r = 0, 1), ranks 2 lane + r; the
         // other members at ranks 255 - (2 lane + r).  Exclusive prefix of cluster
