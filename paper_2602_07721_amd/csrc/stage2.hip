@@ -31,7 +31,7 @@
 // without a sort.  The keys are held in registers (staged in LDS by the second
 // kernel), binned linearly in value over [min, max] (the float bit patterns
 // crowd into a few exponent prefixes), and the boundary bin is ranked by brute force when it holds
-// at most 64 keys, else by 11/11/10-bit radix passes restricted to it.  A list
+// at most 64 keys, else by radix passes of 9 to 11 bits restricted to it.  A list
 // is one query head's candidates (C <= 32768), or, in two passes, first every
 // 4096-candidate slice of a head and then the concatenated winners of its slices
 // (more than 32768 candidates, or more than 8192 for few heads).  With the
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kRrThreads, 8) void compact_rerank_kernel(RetrieveA
     constexpr int kKpt = kChunk / kRrThreads;   // keys per thread
     constexpr int kRrSlots = kRrThreads / 8;    // candidates reranked per block iteration
     constexpr int kWords = kKpt / 4;            // score words per thread
-    static_assert(kKpt >= 4 && kKpt <= 32, "whole score words, one 32-bit mask");
+    static_assert(kKpt >= 8 && kKpt <= 32, "pairs of score words, one 32-bit mask");
     __shared__ float s_tab[16];
     __shared__ uint32_t s_wsum[kRrThreads / 64];
     // The selected keys as offsets in the chunk (2 bytes each, so 16 blocks fit a CU).
@@ -229,13 +229,11 @@ __global__ __launch_bounds__(kRrThreads, 8) void compact_rerank_kernel(RetrieveA
                 ww[4 * u + 2] = t.z;
                 ww[4 * u + 3] = t.w;
             }
-        } else if constexpr (kWords == 2) {
+        } else {
             uint2 t = make_uint2(0, 0);
             if (i0 < a.n) t = *reinterpret_cast<const uint2*>(sp);
             ww[0] = t.x;
             ww[1] = t.y;
-        } else {
-            ww[0] = i0 < a.n ? *reinterpret_cast<const uint32_t*>(sp) : 0u;
         }
     }
     const int l = tid & 7;
@@ -661,9 +659,9 @@ __global__ __launch_bounds__(TH) void topk_lds_kernel(RetrieveArgs a) {
 // Top-k for C <= TH * EPT <= 8192 candidates, held in registers: thread t owns the 4-candidate
 // groups at positions 4 (t + j TH) .. 4 (t + j TH) + 3 for j < EPT / 4, read with
 // coalesced 16-byte loads.  Exact selection on order-preserving uint32 keys: one
-// histogram pass with 2048 bins linear in the estimate over [min, max], then the
-// boundary bin ranked by brute force (at most 64 keys) or by 11/11/10-bit radix
-// passes restricted to it; ties at the k-th key taken in candidate order.  An ordered
+// histogram pass with 2 TH bins linear in the estimate over [min, max], then the
+// boundary bin ranked by brute force (at most 64 keys) or by radix passes of log2(2 TH)
+// bits restricted to it; ties at the k-th key taken in candidate order.  An ordered
 // compaction (a block scan per group of positions) then lists the winners in
 // ascending key index without a sort.
 template <int TH, int EPT, bool kAttend>
