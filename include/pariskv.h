@@ -188,12 +188,13 @@ typedef struct pariskv_ws_layout {
     size_t chunk_sfx;   /* uint32 [batch][Hq][n_chunks][98]: per chunk, #{S >= v}
                            for v = 0 and v_lo <= v <= 97; entries 1 <= v < v_lo
                            hold #{S >= v_lo} (scores below the floor v_lo are
-                           not histogrammed, see thresh)                         */
+                           not histogrammed, see thresh), or, in short rows' chunks
+                           with few scores at the floor, their own counts        */
     size_t chunk_base;  /* int32 [batch][Hq][n_chunks][2]: selected keys (S>theta,
                            S==theta) in earlier chunks                          */
     size_t thresh;      /* int32 [batch][Hq][8]: theta, #(S>theta), quota, C_eff,
-                           the histogram floor v_lo, 1 if the threshold came from
-                           the recount over the stored scores (else 0), 0, 0     */
+                           the histogram floor v_lo, 1 if #{S >= v_lo} < C_eff, so
+                           that scores below it were counted (else 0), 0, 0      */
     size_t cand;        /* int32 [batch][Hq][n_cand]: candidates, ascending      */
     size_t cand_score;  /* float [batch][Hq][n_cand]: RSQ-IP estimates           */
     size_t stats;       /* float [batch][Hq][B][2]: per subspace, sum over the
@@ -299,8 +300,8 @@ int pariskv_workspace_layout(const pariskv_config* cfg, int32_t batch, int64_t n
  * ascending key index: theta is the largest v with #{S >= v} >= min(C, n).
  * The scan histograms only scores at or above a per-head floor v_lo, the
  * integer part of a normal-law estimate of theta from the bonus moments (stats); when
- * #{S >= v_lo} < min(C, n) the threshold is found by an exact recount over
- * the stored scores instead, so the result never depends on the floor.
+ * #{S >= v_lo} < min(C, n) the scores below it are counted exactly from the
+ * stored scores, so the result never depends on the floor.
  * Stage II estimates <k_i, q> for those candidates.
  * Errors: INVALID, UNSUPPORTED (C or k above the served maximum), WORKSPACE, HIP. */
 int pariskv_retrieve(const pariskv_config* cfg, const pariskv_index* index,

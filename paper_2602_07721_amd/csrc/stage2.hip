@@ -77,7 +77,7 @@ struct RowSelect {
 template <int TH>
 struct FoldScratch {
     uint32_t part[TH / 64][4][64];  // per wave: row totals (v = lane, 64 + lane), totals before the chunk
-    uint32_t hist[2][kBins + 1];    // the recount's: whole row, before the chunk
+    uint32_t hist[2][kBins + 1];    // the recount's: the chunk and later ones, the chunks before
 };
 
 // The selection threshold of row `row` and the chunk's bases, as the threshold kernel leaves
@@ -128,29 +128,45 @@ __device__ __forceinline__ RowSelect row_select(const RetrieveArgs& a, int64_t r
     }
     const uint32_t C = (uint32_t)a.c_eff;
     // The counts are exact for v = 0 and v >= the floor: with #{S >= floor} >= C (or floor 1)
-    // theta is found among them, otherwise the row's scores are recounted.
+    // theta is found among them, otherwise the scores below it are counted too.
     const uint32_t at_floor = fl < 64 ? __shfl(tl, (int)fl, 64) : __shfl(thi, (int)fl - 64, 64);
     const bool recount = fl > 1u && at_floor < C;
     if (recount) {
+        // The chunks short of their share were filled in by the scan, and their histograms are
+        // exact; of the others (lane c: chunk c; the same test as there) the scores between 1 and
+        // the floor are counted here, 1024 keys of a chunk at a time, in hist[0] or, before this
+        // block's chunk, hist[1].
+        static_assert(kFoldChunks <= 64, "a lane per chunk");
         for (int i = tid; i < 2 * (kBins + 1); i += TH) (&sm.hist[0][0])[i] = 0;
+        const uint32_t at = sfx[min(lane, nc - 1) * kSfx + fl];
+        const uint64_t open = __ballot(lane < nc && at >= (lane < nc - 1 ? a.share_whole : a.share_last));
         __syncthreads();
         const uint8_t* srow = a.score8 + row * a.n_pad;
-        for (int64_t i = (int64_t)tid * 16; i < a.n; i += (int64_t)TH * 16) {
-            const uint4 w = *reinterpret_cast<const uint4*>(srow + i);  // i + 16 <= n_pad
-            const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-            const bool before = i < chunk * kChunk;  // a chunk is whole 16-byte words
+        constexpr int kParts = kChunk / 1024;
+        for (int p = wave; p < kParts * __popcll(open); p += kWaves) {
+            uint64_t left = open;
+            for (int k = p / kParts; k > 0; --k) left &= left - 1;
+            const int c = __builtin_ctzll(left);
+            const int64_t i = (int64_t)c * kChunk + p % kParts * 1024 + 16 * lane;
+            if (i < a.n) {
+                const uint4 w = *reinterpret_cast<const uint4*>(srow + i);  // i + 16 <= n_pad
+                const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const uint32_t v = (ww[j >> 2] >> (8 * (j & 3))) & 0xffu;
-                if (i + j < a.n) {
-                    atomicAdd(&sm.hist[0][v], 1u);
-                    if (before) atomicAdd(&sm.hist[1][v], 1u);
+                for (int j = 0; j < 16; ++j) {
+                    const uint32_t v = (ww[j >> 2] >> (8 * (j & 3))) & 0xffu;
+                    if (i + j < a.n && v >= 1u && v < fl) atomicAdd(&sm.hist[c < ck ? 1 : 0][v], 1u);
                 }
             }
         }
         __syncthreads();
-        wave_suffix97(sm.hist[0][lane], lane < kBins - 64 ? sm.hist[0][64 + lane] : 0u, lane, &tl, &thi);
-        wave_suffix97(sm.hist[1][lane], lane < kBins - 64 ? sm.hist[1][64 + lane] : 0u, lane, &bl, &bh);
+        uint32_t al, ah, cl, ch;
+        wave_suffix97(sm.hist[0][lane], lane < kBins - 64 ? sm.hist[0][64 + lane] : 0u, lane, &al, &ah);
+        wave_suffix97(sm.hist[1][lane], lane < kBins - 64 ? sm.hist[1][64 + lane] : 0u, lane, &cl, &ch);
+        if (lane == 0) al = cl = 0;  // v = 0 is every key, counted already
+        bl += cl;
+        bh += ch;
+        tl += al + cl;
+        thi += ah + ch;
     }
     int theta;
     uint32_t gt;

@@ -13,12 +13,13 @@ pytestmark = pytest.mark.gpu
 SCALE = 1.0 / np.sqrt(128.0)
 
 
-def _run(batch, hkv, G, n, bud, flags=0, seed=71):
+def _run(batch, hkv, G, n, bud, flags=0, seed=71, K=None):
     """Retrieve on the GPU, two (sequence, KV head) groups checked in full; the run and its read-back."""
     print(f"[dispatch] {batch} x {hkv} x {G}, n {n}, budget {bud}, flags {flags}", flush=True)
     wc = workloads.Config("dispatch", batch=batch, n_kv_heads=hkv, q_per_kv=G, n=n, n_cand=bud[0], n_collide=bud[1],
                           top_k=bud[2], seed=seed)
-    K, V = workloads.layer_kv(wc)
+    law, V = workloads.layer_kv(wc)
+    K = law if K is None else K
     Q, _ = workloads.layer_queries(wc, K)
     signs = workloads.rotation_signs(wc.seed)
     budget = pk.Budget(*bud, flags=flags)
@@ -56,20 +57,107 @@ def test_chunk_and_grid_edges(batch, hkv, G, n, bud):
 
 @pytest.mark.parametrize("batch,hkv,G,n,bud", [(1, 1, 4, 2049, (200, 400, 30)), (1, 2, 4, 70001, (3000, 6000, 64)),
                                                (2, 8, 4, 8 * 4096 + 3, (700, 1400, 64)), (1, 1, 1, 32 * 4096, (60000, 90000, 64))])
-def test_recount_in_the_rerank_equals_the_histogram(batch, hkv, G, n, bud):
+def test_forced_recount_equals_the_histogram(batch, hkv, G, n, bud):
     _, inter = _run(batch, hkv, G, n, bud)
     run, again = _run(batch, hkv, G, n, bud, flags=pk.EXACT_RECOUNT)
     assert np.all(again["thresh"][..., 5] == 1)
     for name in ("cand", "cand_score", "idx", "score"):
         np.testing.assert_array_equal(inter[name].view(np.uint32), again[name].view(np.uint32))
-    # the per-chunk counts below each chunk, documented in the workspace layout
+    _check_chunks(run, again, batch, hkv, G, n, bud[0])
+
+
+def _check_chunks(run, inter, batch, hkv, G, n, C, fills=False):
+    """The per-chunk arrays of two rows, as the workspace layout documents them; with `fills`, how many
+    chunks the scan filled in below the floor and how many it did not."""
     L = run.layout
-    base = run.ws[L["chunk_base"]:L["chunk_base"] + 8 * batch * hkv * G * L["n_chunks"]].cpu().numpy().view(np.int32)
+    rows = batch * hkv * G
+    base = run.ws[L["chunk_base"]:L["chunk_base"] + 8 * rows * L["n_chunks"]].cpu().numpy().view(np.int32)
     base = base.reshape(batch, hkv * G, L["n_chunks"], 2)
-    for s, r in {(0, 0), (batch - 1, hkv * G - 1)}:
-        S, theta = again["S"][s, r, :n].astype(np.int64), again["thresh"][s, r, 0]
+    sfx = run.ws[L["chunk_sfx"]:L["chunk_sfx"] + 392 * rows * L["n_chunks"]].cpu().numpy().view(np.uint32)
+    sfx = sfx.reshape(batch, hkv * G, L["n_chunks"], 98)
+    seen = [0, 0]
+    for s, r in {(0, 0), (0, G - 1), (batch - 1, hkv * G - 1)}:
+        S, theta, floor = inter["S"][s, r, :n].astype(np.int64), inter["thresh"][s, r, 0], int(inter["thresh"][s, r, 4])
         for c in range(L["n_chunks"]):
             assert base[s, r, c, 0] == np.sum(S[:c * 4096] > theta) and base[s, r, c, 1] == np.sum(S[:c * 4096] == theta)
+            if fills:
+                part = S[c * 4096:(c + 1) * 4096]
+                want = np.array([np.sum(part >= v) for v in range(98)])
+                filled = floor > 1 and want[floor] < C * len(part) * 17 // (16 * n) + 1
+                seen[int(filled)] += 1
+                if not filled:
+                    want[1:floor] = want[floor]
+                np.testing.assert_array_equal(sfx[s, r, c], want)
+    return seen
+
+
+def _clustered(batch, hkv, n, clusters, in_runs, seed):
+    """Keys of several modes, their centres 2 sigma apart per coordinate, mixed or one run per mode."""
+    r = np.random.default_rng(seed)
+    K = np.empty((batch, hkv, n, 128), dtype=np.float16)
+    for s in range(batch):
+        for h in range(hkv):
+            centres = np.sqrt(2.0) * r.standard_normal((clusters, 128), dtype=np.float32)
+            of = np.arange(n) * clusters // n if in_runs else r.integers(0, clusters, n)
+            K[s, h] = r.standard_normal((n, 128), dtype=np.float32) + centres[of]
+    return K
+
+
+@pytest.mark.parametrize("batch,hkv,G,n,in_runs", [
+    # rerank blocks of 512 threads: one whole chunk, ragged, 32 chunks; of 256 threads: 9 and 4 chunks
+    (1, 1, 4, 4096, False), (1, 2, 4, 5 * 4096 + 77, False), (1, 2, 4, 5 * 4096 + 77, True), (1, 1, 3, 33000, True),
+    (1, 1, 4, 32 * 4096, True), (2, 8, 4, 9 * 4096 - 100, True), (9, 8, 8, 3 * 4096 + 5, True)])
+def test_floor_above_the_threshold(batch, hkv, G, n, in_runs):
+    # keys of 16 modes and many candidates: the floor lies above most heads' thresholds, so the scan fills
+    # in the chunks short of their share and the rerank counts the rest
+    C = n // 8
+    bud = (C, 2 * C, min(C, 64))
+    K = _clustered(batch, hkv, n, 16, in_runs, 9)
+    run, inter = _run(batch, hkv, G, n, bud, K=K)
+    assert inter["thresh"][..., 5].any()
+    seen = _check_chunks(run, inter, batch, hkv, G, n, C, fills=True)
+    assert seen[1] > 0 and (seen[0] > 0 or not in_runs)
+    _, forced = _run(batch, hkv, G, n, bud, flags=pk.EXACT_RECOUNT, K=K)
+    for name in ("cand", "cand_score", "idx", "score"):
+        np.testing.assert_array_equal(inter[name].view(np.uint32), forced[name].view(np.uint32))
+
+
+def _call_us(K, G, C, k, flags=0):
+    b, h, n, _ = K.shape
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    q = K[:, :, torch.randint(0, n, (G,), generator=gen, device="cuda")].reshape(b, h * G, 128).contiguous()
+    cfg = pk.Config(h, G, n, workloads.rotation_signs(5))
+    index = pk.Index.empty(cfg, b)
+    pk.encode(cfg, index, K)
+    budget = pk.Budget(C, 2 * C, k, flags=flags)
+    idx, _, ws = pk.retrieve(cfg, index, q, n, budget)
+    times = []
+    for _ in range(9):
+        t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        t0.record()
+        for _ in range(20):
+            pk.retrieve(cfg, index, q, n, budget, out_idx=idx, workspace=ws)
+        t1.record()
+        torch.cuda.synchronize()
+        times.append(t0.elapsed_time(t1) * 50)
+    return float(np.median(times))
+
+
+@pytest.mark.parametrize("b,n", [(2, 131072), (12, 65536)])
+def test_a_floor_above_the_threshold_costs_no_second_scan(b, n):
+    # Counting the row in every rerank block made these calls 4 to 8 times those of one mode; one count per
+    # row takes 1.4 to 1.7 times them.  Twice leaves room for the clock, none for the former.
+    print(f"[high floor] {b} x 8 x 4, {n} keys", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    one = torch.randn(b, 8, n, 128, generator=gen, device="cuda", dtype=torch.float16)
+    centres = 2 ** 0.5 * torch.randn(b, 8, 16, 128, generator=gen, device="cuda", dtype=torch.float16)
+    of = torch.randint(0, 16, (b, 8, n, 1), generator=gen, device="cuda").expand(b, 8, n, 128)
+    C = min(n // 8, 16384)
+    plain = _call_us(one, 4, C, 256)
+    many = _call_us(one + torch.gather(centres, 2, of), 4, C, 256)
+    forced = _call_us(one, 4, C, 256, flags=pk.EXACT_RECOUNT)
+    print(f"  one mode {plain:.1f} us, 16 modes {many:.1f}, forced recount {forced:.1f}", flush=True)
+    assert many < 2 * plain and forced < 2 * plain
 
 
 @pytest.mark.parametrize("batch,hkv,G,n,bud", [
