@@ -26,7 +26,8 @@
 // units of 2^-7 and a sum of at most 2^24 of them.  Every partial sum of either part is then
 // exact in float32 in any order, and so are hi + lo and the rest in float64.  lo is carried
 // as 2^11 lo, a normal float16 number.  A tile of 16 keys whose sums of squares may come from
-// a coordinate of 4096 or more (or are not finite) is redone by the float64 butterflies.
+// a coordinate of 4096 or more (or are not finite) is done again with those coordinates as a third
+// operand: multiples of 4 below 2^16, whose sums are exact too.
 //
 // Mapping: a wave takes 16 keys; lane 16 g + r holds coordinates [32 g, 32 g + 32) of
 // key r, i.e. subspaces 4g..4g+3, before and after the transform.  Coordinate 8 s +
@@ -44,10 +45,12 @@
 // What bounds it: vector issue.  A 16-key tile is about 830 vector instructions and 16
 // matrix instructions (1665 vector ones with the transform as float64 butterflies and 7
 // compares per coordinate); the vector unit is busy 3/4 of the time with 3 waves per SIMD.
-// Measured: 8 x 131072 keys 238 -> 136 us, 24 x 10007 keys 177 -> 41 us, most of
+// Measured: 8 x 131072 keys 238 -> 134 us, 24 x 10007 keys 177 -> 38 us, most of
 // the second from blocks sized to fill the chip (launch_encode).  Two waves per SIMD, with
 // the matrix operands held in registers, took 14% longer; summing all 128 inputs on the matrix
-// unit (64 instructions, no float64 stages) 2% longer.
+// unit (64 instructions, no float64 stages) 2% longer.  With a coordinate of 5000 in every tile
+// 238 -> 172 us, in 1 of 6 tiles 168 (340 and 172 when such a tile went through the
+// butterflies, a function of their own, after the matrix path).
 //
 // Each lane counts its 4 ids in an LDS histogram per block, added to global memory
 // once per block; records go through LDS so that a wave stores whole lines.
@@ -99,6 +102,23 @@ __device__ __forceinline__ void split_pair(uint32_t w, uint32_t* hi, uint32_t* l
 
 __device__ __forceinline__ f16x8 frag(const uint32_t (&w)[4]) {
     return __builtin_bit_cast(f16x8, make_uint4(w[0], w[1], w[2], w[3]));
+}
+
+// All ones in the halves of w whose float16 is 4096 or more in size, an infinity or NaN.
+__device__ __forceinline__ uint32_t large_halves(uint32_t w) {
+    // 0x7fff - 0x6bff more sets the top bit of such a half, and carries into none.
+    const uint32_t top = ((w & 0x7fff7fffu) + 0x14001400u) & 0x80008000u;
+    return top | (top - (top >> 15));
+}
+
+// The four matrix steps' sums of one (s, e) combined by two butterfly stages: y[0], y[2], y[4], y[6].
+__device__ __forceinline__ void combine(const double (&v)[4], double* y) {
+    const double t0 = __dadd_rn(v[0], v[1]), t1 = __dsub_rn(v[0], v[1]);
+    const double t2 = __dadd_rn(v[2], v[3]), t3 = __dsub_rn(v[2], v[3]);
+    y[0] = __dadd_rn(t0, t2);
+    y[2] = __dadd_rn(t1, t3);
+    y[4] = __dsub_rn(t0, t2);
+    y[6] = __dsub_rn(t1, t3);
 }
 
 __device__ __forceinline__ double tree8_sum(const double* v) {
@@ -194,6 +214,19 @@ __device__ __forceinline__ Summary summarise(const double* y, const double* Y, d
     return r;
 }
 
+// Sum of squares of the lane's 32 coordinates.  Rounding never takes it below the largest of them:
+// below 2^24 no coordinate is 4096 or more, an infinity or NaN.
+__device__ __forceinline__ float squares(const uint4 (&v)[4]) {
+    float s = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint32_t w[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
+#pragma unroll
+        for (int h = 0; h < 4; ++h) s = __builtin_amdgcn_fdot2(as_f16x2(w[h]), as_f16x2(w[h]), s, false);
+    }
+    return s;
+}
+
 // The 64 bytes of coordinates [32 (lane / 16), +32) of key base + lane % 16 (zeros past the end).
 __device__ __forceinline__ void load_part(const __half* src, int64_t base, int64_t k_end, int lane, uint4 (&v)[4]) {
     const int64_t i = base + (lane & 15);
@@ -204,67 +237,6 @@ __device__ __forceinline__ void load_part(const __half* src, int64_t base, int64
 #pragma unroll
         for (int c = 0; c < 4; ++c) v[c] = p[c];
     }
-}
-
-// y of this lane's 32 coordinates by float64 butterflies: strides 1..16 in registers,
-// 32 and 64 across lanes (16 and 32 lanes away).
-__device__ __forceinline__ void butterflies(const uint4 (&raw)[4], uint32_t smask, int lane, double* x) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const uint32_t w[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
-#pragma unroll
-        for (int h = 0; h < 4; ++h) widen(w[h], &x[8 * c + 2 * h], &x[8 * c + 2 * h + 1]);
-    }
-#pragma unroll
-    for (int j = 0; j < 32; ++j)
-        if ((smask >> j) & 1u) x[j] = -x[j];
-#pragma unroll
-    for (int h = 1; h < 32; h <<= 1) {
-#pragma unroll
-        for (int j = 0; j < 32; ++j) {
-            if ((j & h) == 0) {
-                const double a0 = x[j], a1 = x[j + h];
-                x[j] = __dadd_rn(a0, a1);
-                x[j + h] = __dsub_rn(a0, a1);
-            }
-        }
-    }
-#pragma unroll
-    for (int m = 16; m <= 32; m <<= 1) {
-        const bool upper = (lane & m) != 0;
-#pragma unroll
-        for (int j = 0; j < 32; ++j) {
-            const double p = __shfl_xor(x[j], m, 64);
-            x[j] = upper ? __dsub_rn(p, x[j]) : __dadd_rn(x[j], p);
-            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // few exchanges in flight: registers
-        }
-    }
-}
-
-struct Summaries {
-    Summary s[4];
-};
-
-// This lane's 4 subspaces of key base + lane % 16 by the float64 butterflies: any keys.  Not
-// inlined: it is rare, and its registers would be the kernel's.
-template <bool kAlpha>
-__device__ __attribute__((noinline)) Summaries general_tile(const __half* src, int64_t base, int64_t k_end,
-                                                            uint32_t smask, const double* s_a, const double* s_tau2) {
-    const int lane = threadIdx.x & 63;
-    uint4 raw[4];
-    load_part(src, base, k_end, lane, raw);
-    double x[32];
-    butterflies(raw, smask, lane, x);
-    Summaries r;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        double Y[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) Y[j] = __dmul_rn(x[8 * b + j], x[8 * b + j]);
-        r.s[b] = summarise_any<kAlpha>(x + 8 * b, tree8_sum(Y), s_tau2, s_a);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    return r;
 }
 
 template <bool kLdsCounts, bool kRotate, bool kAlpha>
@@ -279,7 +251,7 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
     __shared__ uint32_t s_cnt[kLdsCounts ? kB * kCentroids : 1];
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int waves = (int)blockDim.x >> 6;
     const int g = lane >> 4, r16 = lane & 15;
     const int64_t grp = blockIdx.y;
@@ -329,15 +301,64 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
     }
     __syncthreads();
 
-    for (int64_t base = k_begin + wave * kTile; base < k_end; base += waves * kTile) {
+    // The tile's records and ids out, and its counts.
+    auto emit = [&](const Summary (&sm)[4], int64_t base, bool count) {
+        uint8_t* stage = s_stage[wave];
+        uint4* st = reinterpret_cast<uint4*>(stage + r16 * kStageRow + 32 * g);
+        st[0] = make_uint4(sm[0].code, sm[1].code, __float_as_uint(sm[0].w), __float_as_uint(sm[1].w));
+        st[1] = make_uint4(sm[2].code, sm[3].code, __float_as_uint(sm[2].w), __float_as_uint(sm[3].w));
+        const int64_t row = grp * capacity + row0 + base;
+        if (base + r16 < k_end) {
+            *reinterpret_cast<uint32_t*>(ids + (row + r16) * kB + 4 * g) =
+                id_slot4(sm[0].id | sm[1].id << 8 | sm[2].id << 16 | sm[3].id << 24);
+            if (count) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int at = (4 * g + b) * kCentroids + (int)sm[b].id;
+                    if (kLdsCounts)
+                        atomicAdd(&s_cnt[at], 1u);
+                    else
+                        atomicAdd(&counts[grp * (kB * kCentroids) + at], 1u);
+                }
+            }
+        }
+        // The wave's own staged rows (LDS operations of a wave complete in order).
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int k = 8 * p + (lane >> 3);
+            const uint4 v = *reinterpret_cast<const uint4*>(stage + k * kStageRow + 16 * (lane & 7));
+            if (base + k < k_end) *reinterpret_cast<uint4*>(rec + (row + k) * kRec + 16 * (lane & 7)) = v;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+
+    // Tiles with large coordinates, left to the second loop: bit t, the wave's t-th.  Where the first
+    // and the middle one have keys that the first loop may leave (a norm of 3000 or so), all are: large
+    // keys then pay for one transform.  A test before it for every tile took 4% of ordinary keys' time.
+    uint32_t later = 0;
+    const int64_t begin = k_begin + wave * kTile;
+    if (kRotate && __any(!(squares(raw) < 0x1p22f))) {
+        const int tiles = (int)((max(k_end - begin, (int64_t)0) + waves * kTile - 1) / (waves * kTile));
+        uint4 mid[4];
+        load_part(src, begin + (int64_t)(tiles / 2) * (waves * kTile), k_end, lane, mid);
+        if (__any(!(squares(mid) < 0x1p22f))) later = 0xffffffffu >> (32 - tiles);
+    }
+    uint32_t bit = 1;
+    for (int64_t base = later ? k_end : begin; base < k_end; base += waves * kTile, bit <<= 1) {
         uint4 cur[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) cur[c] = raw[c];
         load_part(src, base + waves * kTile, k_end, lane, raw);  // the next tile's keys arrive under this one's work
 
         Summary sm[4];
-        double total = 0.0;  // sum of squares of this lane's y
+        bool large = false;
         if (kRotate) {
+            double total = 0.0;  // sum of squares of this lane's y
             uint32_t hi[4][4], lo[4][4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -363,17 +384,11 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
                     double y[8], Y[8];
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
-                        // The four steps' sums combined over j by two butterfly stages.
                         double v[4];
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
                             v[j] = __fma_rn((double)al[j][2 * q + e], 0x1p-11, (double)ah[j][2 * q + e]);
-                        const double t0 = __dadd_rn(v[0], v[1]), t1 = __dsub_rn(v[0], v[1]);
-                        const double t2 = __dadd_rn(v[2], v[3]), t3 = __dsub_rn(v[2], v[3]);
-                        y[e] = __dadd_rn(t0, t2);
-                        y[2 + e] = __dadd_rn(t1, t3);
-                        y[4 + e] = __dsub_rn(t0, t2);
-                        y[6 + e] = __dsub_rn(t1, t3);
+                        combine(v, y + e);
                     }
 #pragma unroll
                     for (int j = 0; j < 8; ++j) Y[j] = __dmul_rn(y[j], y[j]);
@@ -383,12 +398,10 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
                 }
                 __builtin_amdgcn_sched_barrier(0);  // the halves of a tile share registers
             }
-            // A coordinate of 4096 makes the key's squares sum to 2^31 over its 4 lanes.
-            if (__any(!(total < 0x1p28))) {
-                const Summaries again = general_tile<kAlpha>(src, base, k_end, smask, s_a, s_tau2);
-#pragma unroll
-                for (int b = 0; b < 4; ++b) sm[b] = again.s[b];
-            }
+            // A coordinate of 4096 makes the key's squares sum to 2^31 over its 4 lanes, 2^29 in one of
+            // them, less a relative 2^-13 for its inexact sums.
+            large = __any(!(total < 0x1.FFp28));
+            later |= large ? bit : 0u;
         } else {
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
@@ -402,36 +415,63 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
             }
         }
 
-        uint8_t* stage = s_stage[wave];
-        uint4* st = reinterpret_cast<uint4*>(stage + r16 * kStageRow + 32 * g);
-        st[0] = make_uint4(sm[0].code, sm[1].code, __float_as_uint(sm[0].w), __float_as_uint(sm[1].w));
-        st[1] = make_uint4(sm[2].code, sm[3].code, __float_as_uint(sm[2].w), __float_as_uint(sm[3].w));
-        const int64_t row = grp * capacity + row0 + base;
-        if (base + r16 < k_end) {
-            *reinterpret_cast<uint32_t*>(ids + (row + r16) * kB + 4 * g) =
-                id_slot4(sm[0].id | sm[1].id << 8 | sm[2].id << 16 | sm[3].id << 24);
+        emit(sm, base, !large);  // a tile left to the second loop is written over there
+    }
+
+    // The tiles with large coordinates, in a loop of its own so that the two share the registers.
+    if (kRotate) {
+#pragma unroll 1
+        for (; later; later &= later - 1) {
+            const int64_t base = begin + (int64_t)__builtin_ctz(later) * (waves * kTile);
+            uint4 cur[4];
+            load_part(src, base, k_end, lane, cur);
+            const bool finite = !__any(!(squares(cur) < __builtin_huge_valf()));
+            Summary sm[4];
+            int at_lane = lane;
+            asm volatile("" : "+v"(at_lane));
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int at = (4 * g + b) * kCentroids + (int)sm[b].id;
-                if (kLdsCounts)
-                    atomicAdd(&s_cnt[at], 1u);
-                else
-                    atomicAdd(&counts[grp * (kB * kCentroids) + at], 1u);
+            for (int T = 0; T < 2; ++T) {
+                f32x4 ah[4], al[4], at[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t hi[4], lo[4], top[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const uint32_t w = j == 0 ? cur[c].x : j == 1 ? cur[c].y : j == 2 ? cur[c].z : cur[c].w;
+                        const uint32_t mask = large_halves(w);
+                        split_pair(w & ~mask, &hi[c], &lo[c]);
+                        top[c] = w & mask;
+                    }
+                    const f16x8 m = __builtin_bit_cast(f16x8, s_frag[4 * T + j][at_lane]);
+                    ah[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(m, frag(hi), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    al[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(m, frag(lo), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    at[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(m, frag(top), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                }
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    double y[8], Y[8];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        double v[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const double low = __fma_rn((double)al[j][2 * q + e], 0x1p-11, (double)ah[j][2 * q + e]);
+                            v[j] = __dadd_rn(low, (double)at[j][2 * q + e]);
+                        }
+                        combine(v, y + e);
+                    }
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) Y[j] = __dmul_rn(y[j], y[j]);
+                    const double S = tree8_sum(Y);
+                    if (finite)
+                        sm[2 * T + q] = summarise<kAlpha>(y, Y, S, s_bk, s_a);
+                    else
+                        sm[2 * T + q] = summarise_any<kAlpha>(y, S, s_tau2, s_a);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
+            emit(sm, base, true);
         }
-        // The wave's own staged rows (LDS operations of a wave complete in order).
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int k = 8 * p + (lane >> 3);
-            const uint4 v = *reinterpret_cast<const uint4*>(stage + k * kStageRow + 16 * (lane & 7));
-            if (base + k < k_end) *reinterpret_cast<uint4*>(rec + (row + k) * kRec + 16 * (lane & 7)) = v;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 
     if (kLdsCounts) {
@@ -448,6 +488,7 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
 // empty; 64 keys are one step of a block.
 constexpr int64_t kFillBlocks = 768;
 constexpr int64_t kMaxKeysPerBlock = 2048;
+static_assert(kMaxKeysPerBlock <= 32 * kKeysPerIter, "a bit per tile of a wave");
 // Calls of at most one tile per group count straight into global memory.  Scattered global
 // atomics run at about 22 per ns over the chip (64 groups x 600 keys: 28 us with them, 18 us
 // through LDS); for one tile the LDS histogram costs more to clear and flush than it saves.

@@ -97,3 +97,44 @@ def test_append_continues_the_counts(t):
     pk.append(cfg, index, Kd[:, :, 700:].contiguous(), 700)
     for name in ("ids", "rec", "counts"):
         assert torch.equal(getattr(index, name), getattr(whole, name)), name
+
+
+@pytest.mark.parametrize("n,share", [(16, 1.0), (130, 0.5), (1000, 1.0), (150000, 0.5), (150000, 1.0)])
+def test_large_coordinates_beside_the_limit(n, share):
+    # a share of the 16-key tiles has keys of coordinates on both sides of 4096, some in every place of the key;
+    # 150000 keys give a wave 4 tiles, which it sees as all large from the first and the middle one
+    print(f"[encode] n {n}, share {share}", flush=True)
+    r = np.random.default_rng(n)
+    K = r.standard_normal((n, 128), dtype=np.float32)
+    tile = np.arange(n) // 16
+    pick = (r.random(tile[-1] + 1) < share)[tile] & (r.random(n) < 0.5)
+    values = np.array([4094.0, -4094.0, 4096.0, -4096.0, 65504.0, -65504.0, 5000.0, 2.0 ** -24, -0.0])
+    big = r.choice(values, size=(int(pick.sum()), 128))
+    K[pick] = np.where(r.random(big.shape) < r.random((len(big), 1)), big, K[pick])
+    _check(K.astype(np.float16).reshape(1, 1, n, 128))
+
+
+def test_large_keys_cost_no_second_transform():
+    # Keys past the split's limit in every tile take one transform of three operands, 1.3 times the ordinary keys'
+    # time.  After the ordinary one, as a call of its own, it was 2.2 to 2.4 times.
+    def us(K):
+        cfg = pk.Config(8, 4, K.shape[2], workloads.rotation_signs(3))
+        index = pk.Index.empty(cfg, 1)
+        times = []
+        for _ in range(10):
+            t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            t0.record()
+            for _ in range(10):
+                pk.encode(cfg, index, K)
+            t1.record()
+            torch.cuda.synchronize()
+            times.append(t0.elapsed_time(t1) * 100)
+        return float(np.median(times))
+
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    K = torch.randn(1, 8, 131072, 128, generator=gen, device="cuda", dtype=torch.float16)
+    large = K.clone()
+    large[:, :, ::16, 5] = 5000.0
+    plain, past = us(K), us(large)
+    print(f"[encode] ordinary keys {plain:.1f} us, a coordinate of 5000 in every tile {past:.1f}", flush=True)
+    assert past < 1.7 * plain
