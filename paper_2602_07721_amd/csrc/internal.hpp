@@ -297,7 +297,9 @@ constexpr int64_t kRrWideGrid = 2048;
 // Whether every rerank block derives its row's threshold itself, without a threshold launch.
 // Pays where the launch counts and few histograms are read: 1 x 8 heads x 4096 keys 33.7 ->
 // 31.3 us a call, 32 x 32K 35.3 -> 33.0, 256 x 32K (2048 blocks) 51.8 -> 49.0, 32 x 128K
-// (32 chunks) 44.7 -> 42.7.  Past one round of blocks it takes 256-thread blocks (4 waves to
+// (32 chunks) 44.7 -> 42.7.  With up to 64 chunks, twice the histograms in registers, only the
+// smallest grids gain (4 rows x 40 chunks 37.3 -> 33.9; 32 x 33 47.5 -> 51.8, 16 x 64 43.5 ->
+// 47.7).  Past one round of blocks it takes 256-thread blocks (4 waves to
 // read the histograms) where the plain rerank is faster in 128, and pays up to 16 chunks:
 // 1024 x 16K 95.4 -> 90.7, 512 x 32K 77.6 -> 76.4, 384 x 64K 100.8 -> 100.1.
 constexpr int kFoldChunks = 32, kFoldChunksLarge = 16;

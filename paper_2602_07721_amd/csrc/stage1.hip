@@ -164,11 +164,12 @@ __device__ __forceinline__ uint32_t hist_floor(float2 st, int64_t n, int64_t c_e
 // ---------------------------------------------------------------- query + LUT
 
 // Up to this many quads of query heads the 16 subspaces of a quad go to 16 blocks of 4 waves,
-// each wave taking its own head's transform: the rankings spread over four times the CUs, one
-// wave to a SIMD.  8 quads (32 heads x 32K keys) 31.8 -> 30.1 us a call, 32 quads (128 heads x
-// 45K) 45.9 -> 44.4.  From 64 quads on, blocks of 4 subspaces that share the transforms already
-// fill the chip (64 quads of 128K keys 128.2 -> 128.5 with 16 blocks).
-constexpr int64_t kLutNarrow = 32;
+// each wave taking its own head's transform: the rankings spread over four times the CUs, at most
+// 3 waves to a SIMD.  8 quads (32 heads x 32K keys) 31.8 -> 30.1 us a call, 33 quads of 8192 keys
+// 31.7 -> 31.0, 40 of 100K 72.3 -> 71.6, 48 of 8192 32.6 -> 31.9.  With more, blocks of 4 subspaces
+// that share the transforms are no slower (52 quads 32.7 and 32.6, 56 quads 32.8 and 32.9, 64
+// quads of 128K keys 128.2 and 128.5).
+constexpr int64_t kLutNarrow = 48;
 // Past this many (4 blocks of 16 waves a quad: one block per CU) the waves compete for issue
 // and sort 32-bit keys first: 128 quads 9.2 -> 8.5 us, 256 quads 16.0 -> 14.9.  Below, a wave
 // that has to sort again ends the kernel later than the shorter sort makes up (64 quads: a
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(256 * kSubs) void query_lut_kernel(RetrieveArgs a) 
     const bool live = hg < a.g;
     const int64_t row = (int64_t)seq * a.hq + kvh * a.g + hg;
 
-    // Cluster counts of the 4 subspaces, requested first and put in LDS after the
+    // Cluster counts of the block's subspaces, requested first and put in LDS after the
     // transform; the sign word of this lane's coordinates picked without indexing.
     const uint32_t* cnt = a.counts + grp * (kB * kCentroids) + (kSubs * sg) * kCentroids;
     const uint32_t cval = cnt[tid];
@@ -218,9 +219,9 @@ __global__ __launch_bounds__(256 * kSubs) void query_lut_kernel(RetrieveArgs a) 
     (&s_lut[0][0])[tid] = 0u;
     // z = H (s (.) q) of the 4 heads exactly in float64: the wave of head `slot` and
     // subspace `slot` takes it in registers (coordinates 2 lane + r; stride-1 butterflies
-    // inside a lane, the others across lanes) and leaves it in LDS for the other three
-    // waves.  Waves w = 4 slot + sub go to SIMD w mod 4, so the 4 transforms run on 4
-    // different SIMDs.
+    // inside a lane, the others across lanes) and leaves it in LDS for the head's other
+    // waves (with kSubs = 1 there are none, and each wave takes its own).  Waves
+    // w = 4 slot + sub go to SIMD w mod 4, so the 4 transforms run on 4 different SIMDs.
     const bool rotate = !(a.flags & kFlagNoRotation);
     if (sub == slot % kSubs && live) {
         const uint32_t qw = reinterpret_cast<const uint32_t*>(static_cast<const __half*>(a.q) + row * kD)[lane];

@@ -174,10 +174,10 @@ def test_top_k_block_edges(batch, hkv, G, n, bud):
 
 
 @pytest.mark.parametrize("batch,hkv,G", [(4, 8, 4), (11, 3, 4), (4, 4, 8), (11, 1, 10), (3, 11, 1), (8, 8, 4), (13, 5, 2),
-                                         (11, 3, 7)])
+                                         (11, 3, 7), (6, 8, 4), (7, 7, 4), (8, 3, 7), (5, 5, 8)])
 def test_query_block_edges(batch, hkv, G):
-    # 32, 33, 64 and 65 quads of query heads: 1 and 4 subspaces per block, rankings by 64-bit
-    # and by 32-bit keys; partial quads
+    # 32, 33, 48, 49 and 50, 64 and 65 quads of query heads: 1 and 4 subspaces per block, rankings by
+    # 64-bit and by 32-bit keys; partial quads
     _run(batch, hkv, G, 1500, (200, 400, 20))
 
 
