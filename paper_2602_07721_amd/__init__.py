@@ -205,8 +205,12 @@ def _stream(stream):
         return stream.cuda_stream
     torch = _torch()
     if torch.cuda.is_initialized():
-        # torch.cuda.current_stream().cuda_stream without the Stream object (3 us of a small call).
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        # torch.cuda.current_stream().cuda_stream without the Stream object (3 us of a small call),
+        # by names that another torch may not have.
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
     return torch.cuda.current_stream().cuda_stream
 
 

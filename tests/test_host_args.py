@@ -1,5 +1,6 @@
 """The binding's argument checks where a tensor has the right shape and type but not the right
-layout or place, and where an argument is no tensor of the expected rank (no GPU needed)."""
+layout or place, and where an argument is no tensor of the expected rank; the stream a call goes
+to (no GPU needed)."""
 
 import pytest
 import torch
@@ -55,3 +56,17 @@ def test_every_shape_is_checked_before_the_place():
         _call()
     with pytest.raises(ValueError, match="index.ids must have shape"):
         _call(ids=torch.zeros((1, 2, 63, 16), dtype=torch.uint8))
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_the_stream_needs_no_private_name_of_torch(monkeypatch, missing):
+    class Stream:
+        cuda_stream = 4711
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 815, raising=False)
+    assert pk._stream(None) == 815 and pk._stream(Stream()) == 4711
+    monkeypatch.delattr(torch._C, missing)
+    assert pk._stream(None) == 4711
