@@ -217,3 +217,38 @@ def test_equal_estimates_take_the_radix_passes(batch, C, k):
             c, e = inter["cand"][s, h], inter["cand_score"][s, h]
             np.testing.assert_array_equal(inter["idx"][s, h], np.sort(c[np.lexsort((c, -e))[:k]]))
             assert h % 3 or not e.any()
+
+
+@pytest.mark.parametrize("batch,C,k,bins", [
+    # top-k blocks of 256, 512 and 1024 threads, at 4 and at 8 candidates per thread
+    (1, 1000, 102, 512), (1, 2000, 202, 1024), (1, 4000, 302, 2048), (1, 7000, 202, 2048),
+    (9, 2000, 102, 512), (9, 4000, 202, 1024)])
+def test_distinct_estimates_of_one_bin_take_the_radix_passes(batch, C, k, bins):
+    # one key of a thousand times the others' size stretches [min, max], so that the other estimates fall in one
+    # bin; every other key comes four times, so that equal estimates lie across the k-th place (no multiple of 4)
+    n, hkv, G = 8000, 8, 4
+    print(f"[radix] {batch} x {hkv} x {G}, C {C}, k {k}", flush=True)
+    wc = workloads.Config("one bin", batch=batch, n_kv_heads=hkv, q_per_kv=G, n=n // 4, n_cand=C, n_collide=2 * C,
+                          top_k=k, seed=74)
+    K, V = (np.tile(x, (1, 1, 4, 1)) for x in workloads.layer_kv(wc))
+    r = np.random.default_rng(6)
+    Q = (K[:, :, 17, None] + 0.1 * r.standard_normal((batch, hkv, G, 128))).astype(np.float16)
+    K[:, :, 17] *= np.float16(60000) / np.abs(K[:, :, 17]).max(axis=-1, keepdims=True)
+    run = GpuRun(K, V, Q.reshape(batch, hkv * G, 128), workloads.rotation_signs(74), G, pk.Budget(C, 2 * C, k),
+                 SCALE).retrieve()
+    inter = run.intermediates()
+    fused = run.retrieve_attend()
+    np.testing.assert_array_equal(run.out_idx.cpu().numpy(), inter["idx"])
+    np.testing.assert_array_equal(fused.view(np.uint32), run.attend(run.out_idx).view(np.uint32))
+    shared = 0
+    for s in range(batch):
+        for h in range(hkv * G):
+            c, e = inter["cand"][s, h], inter["cand_score"][s, h]
+            order = np.lexsort((c, -e))
+            np.testing.assert_array_equal(inter["idx"][s, h], np.sort(c[order[:k]]))
+            # more than 64 estimates, many of them distinct, in the bin of the k-th: the passes over its digits run
+            of = np.minimum(bins - 1, (e - e.min()) * np.float32(bins) / (e.max() - e.min())).astype(np.int64)
+            among = e[of == of[order[k - 1]]]
+            assert len(among) > 64 and len(np.unique(among)) > 48
+            shared += e[order[k - 1]] == e[order[k]]
+    assert shared > batch * hkv * G // 2
