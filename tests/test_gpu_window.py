@@ -324,6 +324,51 @@ def test_fused_tiered_equals_separate_and_window_paths(n_cand, host):
         np.testing.assert_array_equal(o1h.view(np.uint32), o.cpu().numpy().view(np.uint32))
 
 
+@pytest.mark.parametrize("b,n,n_cand,k,sink,dense", [
+    # lists of 128 and 129, 256 and 257 rows: blocks of 256, 512 and 1024 threads
+    (1, 3000, 700, 64, 16, 48), (1, 3000, 700, 65, 16, 48), (1, 3000, 1500, 192, 16, 48), (1, 3000, 1500, 193, 16, 48),
+    # one dense row, no Sink, fewer keys than k; 288 rows (8 candidates per thread)
+    (2, 2000, 700, 100, 0, 1), (1, 40, 700, 64, 16, 48), (1, 150, 2000, 200, 5, 45), (36, 2500, 2000, 60, 3, 65),
+    (36, 4200, 4000, 150, 40, 66)])
+def test_small_windows_equal_the_separate_calls(b, n, n_cand, k, sink, dense):
+    hkv, g = 2, 4
+    cap = sink + n + dense
+    win = pk.Window(sink, sink, sink + n, cap)
+    wcap = sink + dense + 7
+    print(f"[small window] {b} x {hkv} x {g}, n {n}, C {n_cand}, k {k}, dense {sink} + {dense}", flush=True)
+    K, V = _cache(b, hkv, cap, seed=29)
+    Q = _queries(K, g, seed=29)
+    cfg = pk.Config(hkv, g, n, workloads.rotation_signs(29))
+    budget = pk.Budget(n_cand, 2 * n_cand, k)
+    Kd, Vd, Qd = (torch.from_numpy(x).cuda() for x in (K, V, Q))
+    index = _index_over(cfg, Kd, sink, n)
+    sc1 = torch.empty((b, hkv * g, k), dtype=torch.float32, device="cuda")
+    sc2 = torch.empty_like(sc1)
+    i1, _, _ = pk.retrieve(cfg, index, Qd, n, budget, out_score=sc1)
+    o1 = pk.window_attend(cfg, Qd, Kd, Vd, i1, win, SCALE)
+    i2, _, o2, _ = pk.retrieve_window_attend(cfg, index, Qd, n, budget, Kd, Vd, win, SCALE, out_score=sc2)
+    Kw, Vw = (torch.from_numpy(x).cuda() for x in _window_cache(K, V, win, wcap))
+    # the dense rows of the main cache are wrong on purpose: they must be read from the window cache
+    Kr, Vr = Kd.clone(), Vd.clone()
+    for x in (Kr, Vr):
+        x[:, :, :sink] = 7.0
+        x[:, :, sink + n:] = -3.0
+    i3, _, o3, _ = pk.retrieve_tiered_attend(cfg, index, Qd, n, budget, Kw, Vw, Kr, Vr, win, SCALE)
+    torch.cuda.synchronize()
+    idx = i1.cpu().numpy()
+    np.testing.assert_array_equal(i2.cpu().numpy(), idx)
+    np.testing.assert_array_equal(i3.cpu().numpy(), idx)
+    np.testing.assert_array_equal(sc1.cpu().numpy().view(np.uint32), sc2.cpu().numpy().view(np.uint32))
+    o1 = o1.cpu().numpy()
+    for o in (o2, o3):
+        np.testing.assert_array_equal(o.cpu().numpy().view(np.uint32), o1.view(np.uint32))
+    for s, hq in {(0, 0), (b - 1, hkv * g - 1)}:
+        retrieved = [sink + int(j) for j in idx[s, hq] if j >= 0]
+        assert len(retrieved) == min(k, n)
+        _close(o1[s, hq], owin.window_attention(Q[s, hq], K[s, hq // g], V[s, hq // g], _dense(win), retrieved, SCALE),
+               (s, hq))
+
+
 @pytest.mark.parametrize("to_host", [True, False], ids=["to_pinned_host", "device_to_device"])
 def test_offload_rows_copies_exactly(to_host):
     b, hkv, D = 2, 3, 128
