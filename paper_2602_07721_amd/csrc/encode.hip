@@ -68,7 +68,8 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kTile = 16;                           // keys per wave and iteration
-constexpr int kKeysPerIter = kThreads / 64 * kTile;
+constexpr int kWaves = kThreads / 64;
+constexpr int kKeysPerIter = kWaves * kTile;
 constexpr int kBuckets = 64;                        // of u in [0, 1]; u may round up past 1: more entries
 constexpr int kBucketLut = 2 * kBuckets;            // (a power of two, so that a mask bounds the index)
 constexpr int kFrags = 8;                           // matrix operands: 2 tiles x 4 steps
@@ -247,12 +248,11 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
     __shared__ double s_a[8], s_tau2[7];
     __shared__ Buckets s_bk;
     __shared__ uint4 s_frag[kRotate ? kFrags : 1][64];
-    __shared__ __align__(16) uint8_t s_stage[kThreads / 64][kTile * kStageRow];
+    __shared__ __align__(16) uint8_t s_stage[kWaves][kTile * kStageRow];
     __shared__ uint32_t s_cnt[kLdsCounts ? kB * kCentroids : 1];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int waves = (int)blockDim.x >> 6;
     const int g = lane >> 4, r16 = lane & 15;
     const int64_t grp = blockIdx.y;
     const int64_t k_begin = (int64_t)blockIdx.x * keys_per_block;
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
     // Matrix operands, one uint4 per lane: output (s, e) of tile T in row r16, inputs
     // 8 (4g + c) + 2 j + e', the rotation's signs folded in.
     if (kRotate) {
-        for (int f = wave; f < 8; f += waves) {
+        for (int f = wave; f < kFrags; f += kWaves) {
             const int T = f >> 2, j = f & 3;
             const int so = 4 * (r16 >> 2) + 2 * T + ((r16 >> 1) & 1);
             uint32_t w[4];
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
     }
     if (tid < 8) s_a[tid] = qc.a[tid];
     if (tid < 7) s_tau2[tid] = qc.tau2[tid];
-    for (int i = tid; i < kBucketLut; i += (int)blockDim.x) {
+    for (int i = tid; i < kBucketLut; i += kThreads) {
         // Bins surely passed by every u that may fall in bucket i (rounding may lift it by 1/16
         // of a bucket), and the next threshold.
         const double lo = fmax(0.0, ((double)i - 0.07) / kBuckets);
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
         s_bk.passed[i][0] = c;
     }
     if (kLdsCounts) {
-        for (int i = tid; i < kB * kCentroids; i += (int)blockDim.x) s_cnt[i] = 0;
+        for (int i = tid; i < kB * kCentroids; i += kThreads) s_cnt[i] = 0;
     }
     __syncthreads();
 
@@ -343,17 +343,17 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
     uint32_t later = 0;
     const int64_t begin = k_begin + wave * kTile;
     if (kRotate && __any(!(squares(raw) < 0x1p22f))) {
-        const int tiles = (int)((max(k_end - begin, (int64_t)0) + waves * kTile - 1) / (waves * kTile));
+        const int tiles = (int)((max(k_end - begin, (int64_t)0) + kKeysPerIter - 1) / kKeysPerIter);
         uint4 mid[4];
-        load_part(src, begin + (int64_t)(tiles / 2) * (waves * kTile), k_end, lane, mid);
+        load_part(src, begin + (int64_t)(tiles / 2) * kKeysPerIter, k_end, lane, mid);
         if (__any(!(squares(mid) < 0x1p22f))) later = 0xffffffffu >> (32 - tiles);
     }
     uint32_t bit = 1;
-    for (int64_t base = later ? k_end : begin; base < k_end; base += waves * kTile, bit <<= 1) {
+    for (int64_t base = later ? k_end : begin; base < k_end; base += kKeysPerIter, bit <<= 1) {
         uint4 cur[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) cur[c] = raw[c];
-        load_part(src, base + waves * kTile, k_end, lane, raw);  // the next tile's keys arrive under this one's work
+        load_part(src, base + kKeysPerIter, k_end, lane, raw);  // the next tile's keys arrive under this one's work
 
         Summary sm[4];
         bool large = false;
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
     if (kRotate) {
 #pragma unroll 1
         for (; later; later &= later - 1) {
-            const int64_t base = begin + (int64_t)__builtin_ctz(later) * (waves * kTile);
+            const int64_t base = begin + (int64_t)__builtin_ctz(later) * kKeysPerIter;
             uint4 cur[4];
             load_part(src, base, k_end, lane, cur);
             const bool finite = !__any(!(squares(cur) < __builtin_huge_valf()));
@@ -476,7 +476,7 @@ __global__ __launch_bounds__(kThreads, 3) void encode_kernel(
 
     if (kLdsCounts) {
         __syncthreads();
-        for (int i = tid; i < kB * kCentroids; i += (int)blockDim.x) {
+        for (int i = tid; i < kB * kCentroids; i += kThreads) {
             const uint32_t v = s_cnt[i];
             if (v) atomicAdd(&counts[grp * (kB * kCentroids) + i], v);
         }
