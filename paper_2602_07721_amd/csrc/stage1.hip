@@ -29,11 +29,11 @@
 //                      through range-checked buffer descriptors, so the ragged
 //                      last chunk needs no branches, and each XCD scans whole
 //                      score rows.
-//   threshold_kernel   one block of 16 waves per query head: theta = largest v
+//   threshold_kernel   (long rows and forced recounts; see fold_threshold)
+//                      one block of 16 waves per query head: theta = largest v
 //                      with #{S >= v} >= C_eff, the quota of S == theta keys,
 //                      and per chunk the number of S > theta / S == theta keys
-//                      in earlier chunks.  Not launched for short rows, whose
-//                      rerank blocks derive the same (fold_threshold).
+//                      in earlier chunks.
 // The compaction of the candidates lives with the rerank (stage2.hip).
 
 #include <hip/hip_fp16.h>
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(kColThreads) void collide_kernel(RetrieveArgs a) {
 constexpr int kThrThreads = 1024;  // one block per query head
 constexpr int kThrWaves = kThrThreads / 64;
 
-// kThrUnroll: chunks per wave and load round, the smallest power of two with
+// kThrUnroll: chunks per wave and load round, the smallest power of two from 2 on with
 // 16 kThrUnroll >= n_chunks (at most 16: a 1M-key row in one round).
 template <int kThrUnroll>
 __global__ __launch_bounds__(kThrThreads) void threshold_kernel(RetrieveArgs a) {
