@@ -493,6 +493,7 @@ static_assert(kMaxKeysPerBlock <= 32 * kKeysPerIter, "a bit per tile of a wave")
 // atomics run at about 22 per ns over the chip (64 groups x 600 keys: 28 us with them, 18 us
 // through LDS); for one tile the LDS histogram costs more to clear and flush than it saves.
 constexpr int64_t kDirectCountKeys = 16;
+constexpr int64_t kBulkKeys = 1024;  // calls of fewer keys per group are profiled as appends
 
 __global__ void zero_u32_kernel(uint32_t* p, int64_t count) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -523,7 +524,8 @@ hipError_t launch_encode(const void* keys, int64_t n_src, int64_t src_stride, in
     const bool lds = n_src > kDirectCountKeys;
     const dim3 grid((unsigned)((n_src + per - 1) / per), (unsigned)groups);
     const dim3 block(kThreads);
-    const ProfEvents pe = prof_begin(lds ? "encode" : "append");
+    // The profiler's names: by the size of the call, however it counts.
+    const ProfEvents pe = prof_begin(n_src >= kBulkKeys ? "encode" : "append");
 #define PARISKV_ENCODE(LDS, ROT, ALPHA)                                                                   \
     hipExtLaunchKernelGGL((encode_kernel<LDS, ROT, ALPHA>), grid, block, 0, s, pe.start, pe.stop, 0, k, n_src,   \
                           src_stride, per, row0, capacity, ids, rec, counts, sb, qc)

@@ -319,7 +319,8 @@ inline bool fold_threshold(const RetrieveArgs& a) {
 // the rerank counts only the others.  Both decide by the same counts, #{S >= floor} of the chunk.
 // The share is 1/16 above C keys / n, which is 1 to 2 deviations of a chunk's count: at exactly
 // that, half the chunks of a row just short are left to every rerank block (32 x 128K keys, 16
-// modes, C = n / 8: 61.5 us a call against 47.9; 1/32 above 52.5).  One mode has 2 to 3 times its share.
+// modes, C = n / 8: 61.5 us a call against 47.9; 1/32 above 52.5).  One mode has mostly 2 to 3 times its
+// share.
 // Calls of 16 modes, C = n / 8, with the threshold kernel / every block counting the row / now:
 // 128 x 45679 keys 67.5 / 104.5 / 56.9 us, 64 x 128K 89.2 / 302 / 63.0, 384 x 64K 183 / 432 / 158;
 // one mode pays 0.1 us for the test at the end of a scan block.

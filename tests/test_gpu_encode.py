@@ -99,6 +99,22 @@ def test_append_continues_the_counts(t):
         assert torch.equal(getattr(index, name), getattr(whole, name)), name
 
 
+@pytest.mark.parametrize("t,name", [(1, "append"), (16, "append"), (17, "append"), (1023, "append"), (1024, "encode")])
+def test_profile_names_appends_by_their_size(t, name):
+    cfg = pk.Config(2, 4, t, workloads.rotation_signs(3))
+    index = pk.Index.empty(cfg, 1)
+    index.counts.zero_()
+    K = torch.randn(1, 2, t, 128, device="cuda").half()
+    pk.profile_enable(True)
+    pk.profile_reset()
+    try:
+        pk.append(cfg, index, K, 0)
+        assert set(pk.profile_read()) == {name}
+    finally:
+        pk.profile_enable(False)
+        pk.profile_reset()
+
+
 @pytest.mark.parametrize("n,share", [(16, 1.0), (130, 0.5), (1000, 1.0), (150000, 0.5), (150000, 1.0)])
 def test_large_coordinates_beside_the_limit(n, share):
     # a share of the 16-key tiles has keys of coordinates on both sides of 4096, some in every place of the key;
