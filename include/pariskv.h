@@ -188,8 +188,7 @@ typedef struct pariskv_ws_layout {
     size_t chunk_sfx;   /* uint32 [batch][Hq][n_chunks][98]: per chunk, #{S >= v}
                            for v = 0 and v_lo <= v <= 97; entries 1 <= v < v_lo
                            hold #{S >= v_lo} (scores below the floor v_lo are
-                           not histogrammed, see thresh), or, in short rows' chunks
-                           with few scores at the floor, their own counts        */
+                           not histogrammed, see thresh)                         */
     size_t chunk_base;  /* int32 [batch][Hq][n_chunks][2]: selected keys (S>theta,
                            S==theta) in earlier chunks                          */
     size_t thresh;      /* int32 [batch][Hq][8]: theta, #(S>theta), quota, C_eff,

@@ -614,14 +614,9 @@ static int retrieve_impl(const pariskv_config* cfg, const pariskv_index* index, 
         if (e != hipSuccess) return hip_fail(e, "pad outputs");
         return !att ? PARISKV_OK : group_fetch ? attend_groups() : attend_separately();
     }
-    const bool fold = fold_threshold(a);
-    if (fold) {
-        a.share_whole = refill_share(a, kChunk);
-        a.share_last = refill_share(a, n - (a.n_chunks - 1) * kChunk);
-    }
     if ((e = launch_query_lut(a, s)) != hipSuccess) return hip_fail(e, "query_lut launch");
     if ((e = launch_collide(a, s)) != hipSuccess) return hip_fail(e, "collide launch");
-    if (!fold && (e = launch_threshold(a, s)) != hipSuccess) return hip_fail(e, "threshold launch");
+    if (!fold_threshold(a) && (e = launch_threshold(a, s)) != hipSuccess) return hip_fail(e, "threshold launch");
     if ((e = launch_compact_rerank(a, s)) != hipSuccess) return hip_fail(e, "compact_rerank launch");
     if (group_fetch) {
         if ((e = launch_topk(a, s, false)) != hipSuccess) return hip_fail(e, "topk launch");

@@ -244,8 +244,6 @@ struct RetrieveArgs {
     int64_t n_cand, c_eff;   // row stride of cand / cand_score, and min(C, n)
     int32_t top_k;
     uint32_t flags;  // kFlagNoRotation, kFlagBinary, kFlagRecount
-    // Share of C of a whole and of the last chunk (refill_share); 0: the scan fills no chunk in.
-    uint32_t share_whole, share_last;
     uint32_t cuts[kTierCount];
     // inputs
     const void* q;
@@ -303,29 +301,12 @@ constexpr int64_t kRrWideGrid = 2048;
 // read the histograms) where the plain rerank is faster in 128, and pays up to 16 chunks:
 // 1024 x 16K 95.4 -> 90.7, 512 x 32K 77.6 -> 76.4, 384 x 64K 100.8 -> 100.1.
 constexpr int kFoldChunks = 32, kFoldChunksLarge = 16;
-// A forced recount, which leaves the scan nothing to fill in (refill_share), stays with the
-// threshold kernel: one block per row counts it, where every rerank block would (64 x 128K keys
-// 337 us a call, 76 with the kernel).
+// A forced recount, whose search starts at the top score, stays with the threshold kernel: one
+// block per row counts it.
 inline bool fold_threshold(const RetrieveArgs& a) {
     if (a.flags & kFlagRecount) return false;
     const bool one_round = a.n_chunks * a.batch * a.hq <= kRrWideGrid;
     return a.n_chunks <= (one_round ? kFoldChunks : kFoldChunksLarge);
-}
-
-// With the threshold folded, a row whose floor lies above its threshold would have every rerank
-// block count the whole row again.  Keys of several modes do that often: with 16 modes and C = n / 8
-// most heads.  So the scan itself fills in, in a chunk with fewer scores at the floor than its share
-// of C, the scores below it: where the floor is too high for the row that is nearly every chunk, and
-// the rerank counts only the others.  Both decide by the same counts, #{S >= floor} of the chunk.
-// The share is 1/16 above C keys / n, which is 1 to 2 deviations of a chunk's count: at exactly
-// that, half the chunks of a row just short are left to every rerank block (32 x 128K keys, 16
-// modes, C = n / 8: 61.5 us a call against 47.9; 1/32 above 52.5).  One mode has mostly 2 to 3 times its
-// share.
-// Calls of 16 modes, C = n / 8, with the threshold kernel / every block counting the row / now:
-// 128 x 45679 keys 67.5 / 104.5 / 56.9 us, 64 x 128K 89.2 / 302 / 63.0, 384 x 64K 183 / 432 / 158;
-// one mode pays 0.1 us for the test at the end of a scan block.
-inline uint32_t refill_share(const RetrieveArgs& a, int64_t keys) {
-    return (uint32_t)(a.c_eff * keys * 17 / (16 * a.n)) + 1u;
 }
 
 hipError_t launch_query_lut(const RetrieveArgs& a, hipStream_t s);

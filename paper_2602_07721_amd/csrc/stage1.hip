@@ -23,9 +23,8 @@
 //                      the 4 bytes of one uint32; each is at most 96, so no
 //                      carries), writes S as bytes per head (64 consecutive
 //                      bytes per wave store) and a suffix histogram
-//                      #{S >= v} per head and 4096-key chunk (scores
-//                      at or above the head's floor by LDS atomics into two lane-partitioned
-//                      copies; in a chunk with few of them all, see refill_share).  Loads and stores go
+//                      #{S >= v} per head and 4096-key chunk (scores at or
+//                      above the head's floor by LDS atomics into two lane-partitioned copies).  Loads and stores go
 //                      through range-checked buffer descriptors, so the ragged
 //                      last chunk needs no branches, and each XCD scans whole
 //                      score rows.
@@ -139,9 +138,8 @@ __device__ __forceinline__ void sort128_desc(uint32_t (&key)[2], int lane) {
 // rational approximation of Abramowitz & Stegun 26.2.23 (|error| < 4.5e-4).  Keys that
 // resemble the query tend to be admitted in many subspaces at once, which fattens the
 // upper tail, so for keys of one mode the estimate lies below the true threshold; where it does
-// not (keys of several modes), the scores below it are counted by the threshold kernel or, with
-// the threshold folded into the rerank, by the scan and the rerank (refill_share); the floor
-// never changes a result.  Floor 1 counts every
+// not (keys of several modes), the threshold kernel, or with the threshold folded into the
+// rerank each of its blocks, counts the scores below it (the floor never changes a result).  Floor 1 counts every
 // nonzero score (for p >= 1/2, where little would be saved).  Called by 16 lanes per head,
 // an aligned row of the wave, each with its subspace's moments: every scan block waits for
 // it, and one thread per head walking the 16 subspaces took 0.4 to 0.7 us longer (8 x 8 x
@@ -439,7 +437,6 @@ __global__ __launch_bounds__(kColThreads) void collide_kernel(RetrieveArgs a) {
     uint32_t floor_h[4];
 #pragma unroll
     for (int h = 0; h < 4; ++h) floor_h[h] = s_floor[h];
-    const uint32_t floor_w = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_floor[wave & 3]);  // of head `wave`
     // The floors are the same in every chunk of a row; the first chunk records them for the
     // threshold kernel or the rerank.
     if (chunk == 0 && tid < nh) a.thresh[(row0 + tid) * kThreshRow + 4] = (int32_t)s_floor[tid];
@@ -447,9 +444,6 @@ __global__ __launch_bounds__(kColThreads) void collide_kernel(RetrieveArgs a) {
     const int64_t c0 = chunk * kChunk;
     const int64_t c1 = min(c0 + (int64_t)kChunk, a.n);
     const uint32_t nkeys = (uint32_t)(c1 - c0);
-    // Read here: at the block's end, where it is used, it would be waited for (0.1 us).
-    const uint32_t share = nkeys == (uint32_t)kChunk ? a.share_whole : a.share_last;
-    asm volatile("" ::"s"(share));
 
     // Buffer descriptors over the chunk: the id rows (nkeys x 16 bytes) and each head's
     // score bytes (nkeys, or none for a slot past the quad's last head).  The whole
@@ -502,10 +496,9 @@ __global__ __launch_bounds__(kColThreads) void collide_kernel(RetrieveArgs a) {
     __syncthreads();
 
     // Per-chunk suffix histogram of every head: sfx[v] = #{keys in chunk : S >= v} for
-    // v = 0 and v >= floor; for 0 < v < floor too where the chunk is filled in, else #{S >= floor}.
+    // v = 0 and v >= floor; #{S >= floor} for 0 < v < floor.
     if (wave < nh) {
         const int h = wave;
-        const uint32_t fl = floor_w;
         // Exact count of each value v >= 1: lane holds v = lane and v = 64 + lane.
         auto count_of = [&](int v) -> uint32_t {
             if (v < 1 || v > kMaxScore) return 0u;
@@ -514,50 +507,16 @@ __global__ __launch_bounds__(kColThreads) void collide_kernel(RetrieveArgs a) {
             for (int c = 0; c < kHistCopies; ++c) t += s_hist[(c * 4 + h) * kHistStride + v];
             return t;
         };
+        const uint32_t lo = count_of(lane);
+        const uint32_t hi = count_of(64 + lane);
+        uint32_t sl, sh;
+        wave_suffix97(lo, hi, lane, &sl, &sh);  // exact for v >= floor
+        if (lane == 0) sl = (uint32_t)(c1 - c0);
         uint32_t* dst = a.chunk_sfx + ((row0 + h) * a.n_chunks + chunk) * kSfx;
-        auto store_suffix = [&]() -> uint32_t {  // returns #{S >= floor}
-            const uint32_t lo = count_of(lane);
-            const uint32_t hi = count_of(64 + lane);
-            uint32_t sl, sh;
-            wave_suffix97(lo, hi, lane, &sl, &sh);  // exact for v >= floor
-            const uint32_t at = fl < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)sl, (int)fl)
-                                        : (uint32_t)__builtin_amdgcn_readlane((int)sh, (int)fl - 64);
-            if (lane == 0) sl = nkeys;
-            dst[lane] = sl;
-            if (lane < kSfx - 64) dst[64 + lane] = lane < kBins - 64 ? sh : 0u;
-            return at;
-        };
-        const uint32_t at = store_suffix();
-        if (__builtin_expect(fl > 1u && at < share, 0)) {
-            // Short of its share (see refill_share): the scores below the floor too, from the score
-            // bytes that the block has stored, by the head's own wave.  The whole block doing it
-            // needs a barrier more, which every other block would pay for (0.2 us a call).  Score
-            // rows are padded to a multiple of 64 bytes.
-            const uint8_t* sp = a.score8 + (row0 + h) * a.n_pad + c0;
-            uint4 w[kChunk / 1024];
-#pragma unroll
-            for (int q = 0; q < kChunk / 1024; ++q) {
-                const uint32_t i = 1024u * q + 16u * lane;
-                w[q] = make_uint4(0, 0, 0, 0);
-                if (i < nkeys) w[q] = *reinterpret_cast<const uint4*>(sp + i);
-            }
-#pragma unroll
-            for (int q = 0; q < kChunk / 1024; ++q) {
-                const uint32_t i = 1024u * q + 16u * lane;
-                const uint32_t ww[4] = {w[q].x, w[q].y, w[q].z, w[q].w};
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const uint32_t v = (ww[j >> 2] >> (8 * (j & 3))) & 0xffu;
-                    if (i + j < nkeys && v >= 1u && v < fl) atomicAdd(hcopy + h * kHistStride + v, 1u);
-                }
-            }
-            // The wave's own counters (LDS operations of a wave complete in order).
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            store_suffix();
-        }
+        dst[lane] = sl;
+        if (lane < kSfx - 64) dst[64 + lane] = lane < kBins - 64 ? sh : 0u;
     }
+
 }
 
 // ---------------------------------------------------------------- threshold

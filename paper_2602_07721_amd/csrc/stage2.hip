@@ -77,7 +77,7 @@ struct RowSelect {
 template <int TH>
 struct FoldScratch {
     uint32_t part[TH / 64][4][64];  // per wave: row totals (v = lane, 64 + lane), totals before the chunk
-    uint32_t hist[2][kBins + 1];    // the recount's: the chunk and later ones, the chunks before
+    uint32_t sum[2][TH / 64][2];    // the search's, per pass and wave: counts before the chunk, from it on
 };
 
 // The selection threshold of row `row` and the chunk's bases, as the threshold kernel leaves
@@ -131,61 +131,102 @@ __device__ __forceinline__ RowSelect row_select(const RetrieveArgs& a, int64_t r
     // theta is found among them, otherwise the scores below it are counted too.
     const uint32_t at_floor = fl < 64 ? __shfl(tl, (int)fl, 64) : __shfl(thi, (int)fl - 64, 64);
     const bool recount = fl > 1u && at_floor < C;
-    if (recount) {
-        // The chunks short of their share were filled in by the scan, and their histograms are
-        // exact; of the others (lane c: chunk c; the same test as there) the scores between 1 and
-        // the floor are counted here, 1024 keys of a chunk at a time, in hist[0] or, before this
-        // block's chunk, hist[1].
-        static_assert(kFoldChunks <= 64, "a lane per chunk");
-        for (int i = tid; i < 2 * (kBins + 1); i += TH) (&sm.hist[0][0])[i] = 0;
-        const uint32_t at = sfx[min(lane, nc - 1) * kSfx + fl];
-        const uint64_t open = __ballot(lane < nc && at >= (lane < nc - 1 ? a.share_whole : a.share_last));
-        __syncthreads();
-        const uint8_t* srow = a.score8 + row * a.n_pad;
-        constexpr int kParts = kChunk / 1024;
-        for (int p = wave; p < kParts * __popcll(open); p += kWaves) {
-            uint64_t left = open;
-            for (int k = p / kParts; k > 0; --k) left &= left - 1;
-            const int c = __builtin_ctzll(left);
-            const int64_t i = (int64_t)c * kChunk + p % kParts * 1024 + 16 * lane;
-            if (i < a.n) {
-                const uint4 w = *reinterpret_cast<const uint4*>(srow + i);  // i + 16 <= n_pad
-                const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const uint32_t v = (ww[j >> 2] >> (8 * (j & 3))) & 0xffu;
-                    if (i + j < a.n && v >= 1u && v < fl) atomicAdd(&sm.hist[c < ck ? 1 : 0][v], 1u);
-                }
-            }
-        }
-        __syncthreads();
-        uint32_t al, ah, cl, ch;
-        wave_suffix97(sm.hist[0][lane], lane < kBins - 64 ? sm.hist[0][64 + lane] : 0u, lane, &al, &ah);
-        wave_suffix97(sm.hist[1][lane], lane < kBins - 64 ? sm.hist[1][64 + lane] : 0u, lane, &cl, &ch);
-        if (lane == 0) al = cl = 0;  // v = 0 is every key, counted already
-        bl += cl;
-        bh += ch;
-        tl += al + cl;
-        thi += ah + ch;
-    }
-    int theta;
-    uint32_t gt;
-    theta_of(tl, thi, C, lane, &theta, &gt);
-    theta = __builtin_amdgcn_readfirstlane(theta);
-    auto before = [&](int v) {
-        return v < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)bl, v) : (uint32_t)__builtin_amdgcn_readlane((int)bh, v - 64);
+    auto pick = [](uint32_t lo, uint32_t hi, int v) {
+        return v < 64 ? (uint32_t)__builtin_amdgcn_readlane((int)lo, v) : (uint32_t)__builtin_amdgcn_readlane((int)hi, v - 64);
     };
     RowSelect r;
-    r.theta = (uint32_t)theta;
+    uint32_t gt;
+    if (!recount) {
+        int theta;
+        theta_of(tl, thi, C, lane, &theta, &gt);
+        theta = __builtin_amdgcn_readfirstlane(theta);
+        r.theta = (uint32_t)theta;
+        r.base_g = pick(bl, bh, theta + 1);
+        r.base_e = pick(bl, bh, theta) - r.base_g;
+    } else {
+        // theta is the one v of [lo, hi] with count(v) >= C > count(v + 1).  Every pass over the row's
+        // scores counts two neighbours, from the floor downwards (theta mostly lies 1 or 2 below it),
+        // from the third pass on halving.  Every block of the row does it, so it has to cost little:
+        // scores are at most 96, so adding 128 - v to each byte carries into none and sets its top bit
+        // iff S >= v (as in the compaction), 3 instructions for 4 keys and level and no atomics.
+        // Keys of 16 modes, C = n / 8 (most heads), with the threshold kernel / a histogram of the row
+        // per block / this: 128 rows x 45679 keys 67.6 / 104 / 61.9 us a call, 64 x 128K 89.6 / 302 /
+        // 77.9, 384 x 64K 183 / 430 / 169.
+        static_assert(kFoldChunks * kChunk / kWaves <= 0xffff, "a wave's counts in 16 bits");
+        const uint8_t* srow = a.score8 + row * a.n_pad;
+        const int n = (int)a.n, whole = n & ~15, split = ck * kChunk;
+        int lo = 0, hi = (int)fl - 1;
+        gt = at_floor;  // count(hi + 1), in the row and before the chunk
+        r.base_g = pick(bl, bh, (int)fl);
+        for (int pass = 0;; ++pass) {
+            const int m = pass < 2 ? max(lo, hi - 1) : (lo + hi) >> 1;
+            const uint32_t k0 = (uint32_t)(128 - m) * 0x01010101u, k1 = k0 - 0x01010101u;  // S >= m, S >= m + 1
+            // #{S >= m + 1} + 2^16 #{S >= m} of this thread's 16-key words of [from, to).
+            auto count = [&](int from, int to) -> uint32_t {
+                uint32_t c0 = 0, c1 = 0;
+#pragma unroll 4
+                for (int i = from + 16 * tid; i < to; i += 16 * TH) {
+                    const uint4 w = *reinterpret_cast<const uint4*>(srow + i);
+                    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        c0 += (uint32_t)__popc((ww[q] + k0) & 0x80808080u);
+                        c1 += (uint32_t)__popc((ww[q] + k1) & 0x80808080u);
+                    }
+                }
+                return c0 << 16 | c1;
+            };
+            uint32_t before = count(0, split), after = count(split, whole);
+            if (tid < n - whole) {  // the row's last keys, one each
+                const int v = srow[whole + tid];
+                after += (v >= m ? 0x10000u : 0u) + (v > m ? 1u : 0u);
+            }
+            before = wave_incl_sum(before);
+            after = wave_incl_sum(after);
+            if (lane == 63) {
+                sm.sum[pass & 1][wave][0] = before;
+                sm.sum[pass & 1][wave][1] = after;
+            }
+            __syncthreads();
+            uint32_t b0 = 0, b1 = 0, g0 = 0, g1 = 0;  // count(m), count(m + 1): before the chunk, in the row
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const uint32_t x = sm.sum[pass & 1][w][0], y = sm.sum[pass & 1][w][1];
+                b0 += x >> 16;
+                b1 += x & 0xffffu;
+                g0 += (x >> 16) + (y >> 16);
+                g1 += (x & 0xffffu) + (y & 0xffffu);
+            }
+            b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
+            b1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b1);
+            g0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)g0);
+            g1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)g1);
+            if (g1 >= C) {
+                lo = m + 1;
+                if (lo < hi) continue;
+                r.theta = (uint32_t)hi;
+                r.base_e = b1 - r.base_g;
+                break;
+            }
+            if (g0 >= C) {
+                r.theta = (uint32_t)m;
+                gt = g1;
+                r.base_g = b1;
+                r.base_e = b0 - b1;
+                break;
+            }
+            hi = m - 1;
+            gt = g0;
+            r.base_g = b0;
+        }
+    }
     r.quota = C - gt;
-    r.base_g = before(theta + 1);
-    r.base_e = before(theta) - r.base_g;
     if (tid == 0) {
         int32_t* cb = a.chunk_base + (row * a.n_chunks + chunk) * 2;
         cb[0] = (int32_t)r.base_g;
         cb[1] = (int32_t)r.base_e;
         if (chunk == 0) {  // t[4] stays the scan's: the other blocks read it
-            t[0] = theta;
+            t[0] = (int32_t)r.theta;
             t[1] = (int32_t)gt;
             t[2] = (int32_t)r.quota;
             t[3] = (int32_t)C;
